@@ -204,3 +204,25 @@ def test_wg_batch_fp32_matches_single_solves():
                          allow_not_converged=True)
         assert ib.cycles == i1.cycles and ib.status == i1.status, i
         assert np.array_equal(host(X), host(X1)), i
+
+
+# sizes at the body's edges: grids of a few points (one masked tile), exactly
+# one full tile and one point more, 8 and 9 tiles (either reduction tree); s
+# around the eight sweeps that carry the residual sum between them
+@pytest.mark.parametrize("n,tile,ov", [(1, 64, 0), (2, 64, 0), (3, 128, 10), (64, 64, 6), (65, 64, 6), (406, 64, 14),
+                                       (407, 64, 15), (511, 512, 0), (1030, 512, 40)])
+@pytest.mark.parametrize("s", [1, 7, 8, 9, 10])
+def test_wg_tile_and_sweep_edges_match_oracle(orc, n, tile, ov, s):
+    f = W.rhs_random(n, 11)
+    x0 = W.rhs_random(n, 12)
+    h = 1.0 / (n + 1)
+    say(f"wg edges n={n} tile={tile} s={s} ov={ov}")
+    for nc in (1, 2, 5):
+        X = dev(x0)
+        hj.solve_1d(dev(f), X, h, tile=tile, s=s, overlap=ov, rel_tol=0.0, max_cycles=nc)
+        assert np.array_equal(host(X), orc.hier_1d(f, x0, h, tile, s, nc, ov))
+    X = dev(x0)
+    info = hj.solve_1d(dev(f), X, h, tile=tile, s=s, overlap=ov, rel_tol=1e-2, max_cycles=30, allow_not_converged=True)
+    xo, co, relo, r0o = orc.solve_1d(f, x0, h, tile=tile, s=s, tol=1e-2, max_cycles=30, overlap=ov)
+    assert info.cycles == (co if co >= 0 else 30) and np.array_equal(host(X), xo)
+    assert abs(info.rel_residual - relo) <= 1e-12 * relo and abs(info.r0_norm - r0o) <= 1e-12 * r0o
