@@ -56,14 +56,6 @@ namespace {
 constexpr double kU32 = 5.9604644775390625e-08;  // 2^-24, FP32 unit roundoff
 constexpr double kLn2 = 0.6931471805599453;
 
-template <int NT>
-__device__ __forceinline__ void post_partial_at(double mine, double *slot)
-{
-    __shared__ double red[NT / 64];
-    const double bs = block_sum<NT>(mine, red);
-    if (threadIdx.x == 0) *slot = bs;
-}
-
 constexpr int kRBX = 64, kRRPT = 8;  // refinement-step 2D blocks: 64 columns x (4 x 8) rows
 constexpr int kR1 = 2048;           // refinement-step 1D blocks
 
@@ -140,7 +132,7 @@ void k_batch_cycle2d(const BProb *__restrict__ probs,
     } else {
         rsq = ref_blocks<NT>(P, S, tile, P.nitems);
     }
-    post_partial_at<NT>(rsq, &part[P.part0 + tile]);
+    post_partial<NT>(rsq, &part[P.part0 + tile]);
 }
 
 template <int M, int TT>
@@ -175,7 +167,7 @@ __global__ __launch_bounds__(kNT) void k_batch_cycle1d(const BProb *__restrict__
     } else {
         rsq = ref_blocks<kNT>(P, S, blk, P.nitems);
     }
-    post_partial_at<kNT>(rsq, &part[P.part0 + blk]);
+    post_partial<kNT>(rsq, &part[P.part0 + blk]);
 }
 
 // Variable-coefficient 2D problems (dim 3, FP64, plain): the tile bodies of
@@ -196,7 +188,7 @@ __global__ __launch_bounds__((vc_threads<TX, TY>())) void k_batch_cycle_vc(const
     main_arrays<double>(P, S, xin, xout);
     const int tile = (int)(w - P.item0);
     const double rsq = tile_vc<TX, TY, true>(P.gv, tile, (const double *)P.f, xin, xout, s);
-    post_partial_at<vc_threads<TX, TY>()>(rsq, &part[P.part0 + tile]);
+    post_partial<vc_threads<TX, TY>()>(rsq, &part[P.part0 + tile]);
 }
 
 // ---------------------------------------------------------------- judge
@@ -248,7 +240,7 @@ __device__ __forceinline__ bool switch_now(const BProb &P, BState &t, double acc
     return true;
 }
 
-// Lane 0 of the problem's wavefront.  acc: sum of the partials of this step
+// One lane of the problem's wavefront.  acc: sum of the partials of this step
 // (the cycle's residual of iterate j, or the refinement step's FP64
 // residual of the new x).
 __device__ void judge_problem(const BProb &P, BState &t, double acc, const BRefine &rf)
@@ -344,15 +336,16 @@ __device__ void judge_problem(const BProb &P, BState &t, double acc, const BRefi
     }
 }
 
+// in lane 63
 __device__ __forceinline__ double sum_parts(const double *base, int64_t n, int lane)
 {
     double acc = 0.0;
     for (int64_t i = lane; i < n; i += 64) acc += base[i];
-    return wave_sum(acc);
+    return wave_sum63(acc);
 }
 
 // One wavefront per problem: partials summed lane-strided in index order,
-// then a fixed butterfly; lane 0 updates the state.
+// then over the lanes in a fixed order; lane 63 updates the state.
 __global__ __launch_bounds__(256) void k_batch_judge(const BProb *__restrict__ probs, int nprob,
                                                      BState *state, const double *part, BRefine rf)
 {
@@ -362,7 +355,7 @@ __global__ __launch_bounds__(256) void k_batch_judge(const BProb *__restrict__ p
     if (state[p].status != ST_RUNNING) return;
     const BProb &P = probs[p];
     const double acc = sum_parts(part + P.part0, P.nitems, lane);
-    if (lane == 0) {
+    if (lane == 63) {
         BState t = state[p];
         judge_problem(P, t, acc, rf);
         state[p] = t;

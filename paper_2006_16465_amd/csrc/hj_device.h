@@ -77,27 +77,62 @@ __device__ inline int xcd_tile(int b, int nb)
 }
 
 // ---------------------------------------------------------------------------
-// Deterministic sums: 64-lane butterfly, then waves in index order.
+// Deterministic sums: a wavefront by DPP steps, then wavefronts in index order.
 // ---------------------------------------------------------------------------
-__device__ inline double wave_sum(double v)
+// v from the lane CTRL selects, 0 in rows ROW_MASK leaves out.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_or_zero(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROW_MASK, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-template <int NT>
-__device__ inline double block_sum(double v, double *red /* NT/64 doubles of LDS */)
+// One of the six steps of a sum over the 64 lanes of a wavefront (all lanes
+// active); after them lane 63 holds it.  Quads, half rows and rows of 16 by
+// lane permutations, then rows 0+1 and 2+3 by broadcasts of lane 15 of a row
+// into the next.
+template <int STEP>
+__device__ __forceinline__ double wave_step(double v)
 {
-    v = wave_sum(v);
+    constexpr int ctrl[6] = {
+        0xb1,   // quad_perm [1,0,3,2]
+        0x4e,   // quad_perm [2,3,0,1]
+        0x141,  // row_half_mirror
+        0x140,  // row_mirror
+        0x142,  // row_bcast:15 into rows 1 and 3
+        0x143,  // row_bcast:31 into rows 2 and 3
+    };
+    constexpr int rows[6] = {0xf, 0xf, 0xf, 0xf, 0xa, 0xc};
+    return v + dpp_or_zero<ctrl[STEP], rows[STEP]>(v);
+}
+
+// The sum over the wavefront, in lane 63 (a butterfly of lane shuffles goes
+// through LDS, six dependent round trips of it).
+__device__ __forceinline__ double wave_sum63(double v)
+{
+    v = wave_step<0>(v);
+    v = wave_step<1>(v);
+    v = wave_step<2>(v);
+    v = wave_step<3>(v);
+    v = wave_step<4>(v);
+    return wave_step<5>(v);
+}
+
+// Sum over a workgroup of NT threads, in every thread.  red: NT / 64 doubles
+// of LDS that no earlier use of the workgroup still reads.
+template <int NT>
+__device__ inline double block_sum(double v, double *red)
+{
+    v = wave_sum63(v);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __syncthreads();  // red may still be in use by a previous call
-    if (lane == 0) red[wid] = v;
+    if (lane == 63) red[wid] = v;
     __syncthreads();
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < NT / 64; ++w) t += red[w];
-    return t;  // identical in every thread
+    return t;
 }
 
 // Decide convergence for iterate c from its squared residual norm.  Once a
@@ -140,27 +175,31 @@ __device__ inline int32_t read_status(const Ctrl *ctrl)
 }
 
 // Residual bookkeeping handed to every kernel that reduces ||r||^2.
-// Each workgroup stores its partial sum in part_cur[blockIdx.x] with a plain
+// Each workgroup stores its partial sum in its slot of part_cur with a plain
 // store.  The sum over the grid is formed by workgroup 0 of the NEXT kernel on
 // the stream (the kernel boundary makes the partials visible), which judges
 // iterate c - 1; no atomics and no cache-flushing fences inside the grid.
+// That workgroup does nothing else: such a kernel launches one workgroup more
+// than it has tiles (with a tile of its own to do after the verdict it ended
+// last, about 1 us of every cycle on grids of a few hundred tiles).
 struct Red {
-    double *part_cur;         // this kernel's partials (one per workgroup)
+    double *part_cur;         // this kernel's partials (one per tile or block)
     const double *part_prev;  // the previous kernel's partials
     Ctrl *ctrl;
     int64_t c;                // index of the iterate this kernel evaluates
-    int nb_prev;              // workgroups of the previous kernel (0: nothing to judge)
+    int nb_prev;              // partials of the previous kernel (0: nothing to judge)
 };
 
 // Sum n partials in a fixed order and judge iterate c (one workgroup).
-// Thread t adds chunks of 8 consecutive partials; 4 chunks (32 loads) are in
-// flight per thread before any add, so a 64-lane workgroup reads 16K partials
-// in a few memory latencies instead of one latency per partial.
+// Thread t adds chunks of 8 consecutive partials; U chunks are in flight per
+// thread before any add, so a workgroup reads 2K partials or more in one memory
+// latency.  U falls with the workgroup's size: 32 loads in flight a thread hold
+// 64 VGPRs, more than an FP32 tile needs for its sweeps.
 template <int NT>
 __device__ inline void judge_partials(const double *part, int n, Ctrl *ctrl, int64_t c, double tol)
 {
     __shared__ double red[NT / 64];
-    constexpr int V = 8, U = 4;
+    constexpr int V = 8, U = NT >= 256 ? 1 : NT >= 128 ? 2 : 4;
     double acc = 0.0;
     for (int base = 0; base < n; base += NT * V * U) {
         double v[U][V];
@@ -184,12 +223,37 @@ __device__ inline void judge_partials(const double *part, int n, Ctrl *ctrl, int
     if (threadIdx.x == 0) judge(ctrl, c, tot, tol);
 }
 
+// Start of a kernel that reduces ||r||^2 and judges: false for workgroups
+// with nothing (more) to do.  The others are numbered by judged_block.  LATE:
+// the caller asks stopped() itself, once its loads are under way.
+template <int NT, bool LATE = false>
+__device__ inline bool judged_start(const Red &red, double tol)
+{
+    if (!LATE && stopped(red.ctrl, red.c)) return false;
+    if (blockIdx.x > 0) return true;
+    if (red.nb_prev > 0) judge_partials<NT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
+    return false;
+}
+
+// Number of this workgroup and how many there are; JUDGED: workgroup 0 left out.
+template <bool JUDGED>
+__device__ inline int judged_block()
+{
+    return (int)blockIdx.x - (JUDGED ? 1 : 0);
+}
+
+template <bool JUDGED>
+__device__ inline int judged_blocks()
+{
+    return (int)gridDim.x - (JUDGED ? 1 : 0);
+}
+
 template <int NT>
-__device__ inline void post_partial(double mine, double *part_cur)
+__device__ inline void post_partial(double mine, double *slot)
 {
     __shared__ double red[NT / 64];
     const double bs = block_sum<NT>(mine, red);
-    if (threadIdx.x == 0) part_cur[blockIdx.x] = bs;
+    if (threadIdx.x == 0) *slot = bs;
 }
 
 }  // namespace hj

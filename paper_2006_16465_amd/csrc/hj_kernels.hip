@@ -32,11 +32,8 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
                                                  int s, Red red, double tol)
 {
     static_assert(kNT % TX == 0 && (TX * TY) % kNT == 0, "tile/threads mismatch");
-    if (RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<kNT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
+    if (RES && !judged_start<kNT>(red, tol)) return;
+    const int blk = judged_block<RES>(), nblk = judged_blocks<RES>();
 
     constexpr int P = TX + 2;          // LDS row pitch, halo column each side
     constexpr int R = TY + 2;          // LDS rows, halo row each side
@@ -44,7 +41,7 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
     constexpr int RSTEP = kNT / TX;
     __shared__ T buf[2][R * P];
 
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_tile(blk, nblk);
     const int bi = tile / g.ntx, bj = tile - bi * g.ntx;
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
     const int c0 = axis_origin(g.nx, TX, g.ox, bj);
@@ -124,28 +121,30 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
         if (col_own && r >= rlo && r < rhi) xout[(int64_t)(r0 + r) * ld + c0 + tc] = val[j];
     }
 
-    if (RES) post_partial<kNT>(rsq, red.part_cur);
+    if (RES) post_partial<kNT>(rsq, &red.part_cur[blk]);
 }
 
 // ============================================================================
 // 2D hierarchical cycle, register-resident: one workgroup of W wavefronts per
 // full tile (tile body in hj_tiles.h), fused residual of the incoming iterate.
+// FEW: the shape for grids of few tiles; the early-exit flag is asked for once
+// the tile's loads are under way (one memory latency instead of two), which
+// costs launches after the verdict a tile load each, little on such grids.
 // ============================================================================
-template <typename T, int C, int R, int W, bool RES, bool ISO>
+template <typename T, int C, int R, int W, bool RES, bool ISO, bool FEW>
 __global__ __launch_bounds__(64 * W, (min_waves_2d<T, C, R>())) void k_cycle2d_reg(Geom2 g, const T *__restrict__ f,
                                                         const T *__restrict__ xin,
                                                         T *__restrict__ xout, int nsub, Red red,
                                                         double tol)
 {
     constexpr int NT = 64 * W;
-    if (RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<NT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
-    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, rotate_rows<T>()>(g, xcd_tile(blockIdx.x, gridDim.x), f, xin,
-                                                         xout, nsub);
-    if (RES) post_partial<NT>(rsq, red.part_cur);
+    if (RES && !judged_start<NT, FEW>(red, tol)) return;
+    const int blk = judged_block<RES>();
+    const int tile = xcd_tile(blk, judged_blocks<RES>());
+    auto stop = [&] { return RES && FEW && stopped(red.ctrl, red.c); };
+    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, !FEW && rotate_rows<T>(), 0>(g, tile, f, xin, xout, nsub, stop);
+    if (RES && FEW && rsq < 0.0) return;
+    if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
 }
 
 // ============================================================================
@@ -160,13 +159,11 @@ __global__ __launch_bounds__(kNT) void k_sweep2d(Geom2 g, const T *__restrict__ 
                                                  const T *__restrict__ xin, T *__restrict__ xout,
                                                  Red red, double tol)
 {
-    if (SWEEP && RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<kNT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
+    constexpr bool judged = SWEEP && RES;
+    if (judged && !judged_start<kNT>(red, tol)) return;
+    const int blk = judged_block<judged>(), nblk = judged_blocks<judged>();
     const int gx = (g.nx + kSBX - 1) / kSBX;
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int b = xcd_tile(blk, nblk);
     const int by = b / gx, bx = b - by * gx;
     const int c = bx * kSBX + (int)(threadIdx.x % kSBX);
     const int rbeg = (by * kSBY + (int)(threadIdx.x / kSBX)) * kSRPT;
@@ -197,7 +194,7 @@ __global__ __launch_bounds__(kNT) void k_sweep2d(Geom2 g, const T *__restrict__ 
             }
         }
     }
-    if (RES) post_partial<kNT>(rsq, red.part_cur);
+    if (RES) post_partial<kNT>(rsq, &red.part_cur[blk]);
 }
 
 // ============================================================================
@@ -208,13 +205,10 @@ __global__ __launch_bounds__(kNT) void k_cycle1d(Geom1 g, const T *__restrict__ 
                                                  const T *__restrict__ xin, T *__restrict__ xout,
                                                  int s, Red red, double tol)
 {
-    if (RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<kNT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
-    const double rsq = tiles_1d<T, TT, RES>(g, xcd_tile(blockIdx.x, gridDim.x), f, xin, xout, s);
-    if (RES) post_partial<kNT>(rsq, red.part_cur);
+    if (RES && !judged_start<kNT>(red, tol)) return;
+    const int blk = judged_block<RES>(), nblk = judged_blocks<RES>();
+    const double rsq = tiles_1d<T, TT, RES>(g, xcd_tile(blk, nblk), f, xin, xout, s);
+    if (RES) post_partial<kNT>(rsq, &red.part_cur[blk]);
 }
 
 // 1D classical sweep / residual: one point per thread.
@@ -223,12 +217,10 @@ __global__ __launch_bounds__(kNT) void k_sweep1d(Geom1 g, const T *__restrict__ 
                                                  const T *__restrict__ xin, T *__restrict__ xout,
                                                  Red red, double tol)
 {
-    if (SWEEP && RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<kNT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
-    const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kNT + threadIdx.x;
+    constexpr bool judged = SWEEP && RES;
+    if (judged && !judged_start<kNT>(red, tol)) return;
+    const int blk = judged_block<judged>(), nblk = judged_blocks<judged>();
+    const int64_t i = (int64_t)xcd_tile(blk, nblk) * kNT + threadIdx.x;
     double rsq = 0.0;
     if (i < g.n) {
         const T w = i > 0 ? xin[i - 1] : T(0);
@@ -241,7 +233,7 @@ __global__ __launch_bounds__(kNT) void k_sweep1d(Geom1 g, const T *__restrict__ 
             rsq += rr * rr;
         }
     }
-    if (RES) post_partial<kNT>(rsq, red.part_cur);
+    if (RES) post_partial<kNT>(rsq, &red.part_cur[blk]);
 }
 
 __global__ void k_ctrl_init(Ctrl *ctrl, double sw_tol, int64_t sw_min_c)
@@ -271,24 +263,25 @@ constexpr bool lds_shape(int tx, int ty)
     return (tx == 16 || tx == 32 || tx == 64) && (ty == 16 || ty == 32 || ty == 64);
 }
 
-template <typename T, int TX, int TY>
+// The FEW shape is taken where the tiles of the ordinary one have no more
+// wavefronts than the chip has SIMDs (4 on each of 256 CUs): each then runs
+// alone on its SIMD and a sweep takes as long as its own chain.  Measured, us
+// per FP64 cycle, ordinary / FEW shape: 32 x 32 tiles at s = 16, 512^2 (256
+// wavefronts) 8.3 / 5.8, 1024^2 (1 024) 10.9 / 9.8, 4096^2 (16 384) 90 / 98;
+// 64 x 64 at s = 10, 512^2 (484) 8.5 / 8.3, 1024^2 (1 936) 12.0 / 12.3.
+constexpr int64_t kSimds = 1024;
+
+template <typename T, int C, int R, int W, bool FEW>
 hipError_t cyc2_reg(const Geom2 &g, int s, bool res, const void *f, const void *xin, void *xout,
                     const Red &red, double tol, hipStream_t st)
 {
-    using S = RegShape<TX, TY>;
-    constexpr int C = S::C, R = S::R, W = S::W;
-    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty);
-    const T *F = (const T *)f;
-    const T *XI = (const T *)xin;
-    T *XO = (T *)xout;
-    if (res) {
-        if (g.iso) k_cycle2d_reg<T, C, R, W, true, true><<<nb, 64 * W, 0, st>>>(g, F, XI, XO, s, red, tol);
-        else k_cycle2d_reg<T, C, R, W, true, false><<<nb, 64 * W, 0, st>>>(g, F, XI, XO, s, red, tol);
-    } else {
-        if (g.iso) k_cycle2d_reg<T, C, R, W, false, true><<<nb, 64 * W, 0, st>>>(g, F, XI, XO, s, red, tol);
-        else k_cycle2d_reg<T, C, R, W, false, false><<<nb, 64 * W, 0, st>>>(g, F, XI, XO, s, red, tol);
-    }
-    return hipGetLastError();
+    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
+    auto go = [&](auto kernel) {
+        kernel<<<nb, 64 * W, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
+        return hipGetLastError();
+    };
+    if (res) return g.iso ? go(k_cycle2d_reg<T, C, R, W, true, true, FEW>) : go(k_cycle2d_reg<T, C, R, W, true, false, FEW>);
+    return g.iso ? go(k_cycle2d_reg<T, C, R, W, false, true, FEW>) : go(k_cycle2d_reg<T, C, R, W, false, false, FEW>);
 }
 
 template <typename T, int TX, int TY>
@@ -296,11 +289,18 @@ hipError_t cyc2(const Geom2 &g, int s, bool res, const void *f, const void *xin,
                 const Red &red, double tol, hipStream_t st)
 {
     if constexpr (RegShape<TX, TY>::ok) {
-        if (g.reg && g.nx >= TX && g.ny >= TY)
-            return cyc2_reg<T, TX, TY>(g, s, res, f, xin, xout, red, tol, st);
+        if (g.reg && g.nx >= TX && g.ny >= TY) {
+            using S = RegShape<TX, TY>;
+            using F = FewShape<TX, TY>;
+            if constexpr (F::ok) {
+                if ((int64_t)g.ntx * g.nty * S::W <= kSimds)
+                    return cyc2_reg<T, F::C, F::R, F::W, true>(g, s, res, f, xin, xout, red, tol, st);
+            }
+            return cyc2_reg<T, S::C, S::R, S::W, false>(g, s, res, f, xin, xout, red, tol, st);
+        }
     }
     if constexpr (lds_shape(TX, TY)) {
-        const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty);
+        const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
         const T *F = (const T *)f;
         const T *XI = (const T *)xin;
         T *XO = (T *)xout;
@@ -337,7 +337,7 @@ template <typename T, int TT>
 hipError_t cyc1(const Geom1 &g, int s, bool res, const void *f, const void *xin, void *xout,
                 const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)cycle1d_blocks(g);  // the count the judge sums partials over
+    const unsigned nb = (unsigned)cycle1d_blocks(g) + (res ? 1 : 0);
     if (res) k_cycle1d<T, TT, true><<<nb, kNT, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
     else k_cycle1d<T, TT, false><<<nb, kNT, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
     return hipGetLastError();
@@ -411,7 +411,7 @@ template <typename T>
 static hipError_t sw2(const Geom2 &g, bool res, const void *f, const void *xin, void *xout,
                       const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)sweep2d_blocks(g);
+    const unsigned nb = (unsigned)sweep2d_blocks(g) + (res ? 1 : 0);
     const T *F = (const T *)f;
     const T *XI = (const T *)xin;
     T *XO = (T *)xout;
@@ -456,7 +456,7 @@ hipError_t launch_cycle1d(int dt, const Geom1 &g, int s, bool res, const void *f
 hipError_t launch_sweep1d(int dt, const Geom1 &g, bool res, const void *f, const void *xin,
                           void *xout, const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)sweep1d_blocks(g);
+    const unsigned nb = (unsigned)sweep1d_blocks(g) + (res ? 1 : 0);
     if (dt == F64) {
         if (res) k_sweep1d<double, true, true><<<nb, kNT, 0, st>>>(g, (const double *)f, (const double *)xin, (double *)xout, red, tol);
         else k_sweep1d<double, false, true><<<nb, kNT, 0, st>>>(g, (const double *)f, (const double *)xin, (double *)xout, red, tol);

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void k_resid2d_f64_to_f32(Geom2 g, const doubl
             }
         }
     }
-    post_partial<256>(rsq, part);
+    post_partial<256>(rsq, &part[blockIdx.x]);
 }
 
 // x += (double)e over the interior (pitched rows)

@@ -54,35 +54,6 @@ hipError_t allow_lds(K kernel, size_t lds)
     return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-// v from lane CTRL selects, 0 in rows ROW_MASK leaves out.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_or_zero(double v)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROW_MASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROW_MASK, 0xf, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-// One of the six steps of a sum over the 64 lanes of a wavefront (all lanes
-// active); after them lane 63 holds it.  Quads, half rows and rows of 16 by
-// lane permutations, then rows 0+1 and 2+3 by broadcasts of lane 15 of a row
-// into the next.
-template <int STEP>
-__device__ __forceinline__ double wave_step(double v)
-{
-    constexpr int ctrl[6] = {
-        0xb1,   // quad_perm [1,0,3,2]
-        0x4e,   // quad_perm [2,3,0,1]
-        0x141,  // row_half_mirror
-        0x140,  // row_mirror
-        0x142,  // row_bcast:15 into rows 1 and 3
-        0x143,  // row_bcast:31 into rows 2 and 3
-    };
-    constexpr int rows[6] = {0xf, 0xf, 0xf, 0xf, 0xa, 0xc};
-    return v + dpp_or_zero<ctrl[STEP], rows[STEP]>(v);
-}
-
 // Sum of the wavefront sums of one cycle: a fixed tree over SL slots (slots
 // of wavefronts the workgroup does not have hold 0, so SL = 8 and SL = 16 add
 // the same numbers in the same order).
@@ -246,15 +217,6 @@ __device__ __forceinline__ void solve_body(const Geom1 &g, const T *__restrict__
     auto post = [&](int par, double sum) {
         if (lane == 63) red[par][wave] = sum;
     };
-    auto finish = [&](double v) {
-        v = wave_step<0>(v);
-        v = wave_step<1>(v);
-        v = wave_step<2>(v);
-        v = wave_step<3>(v);
-        v = wave_step<4>(v);
-        return wave_step<5>(v);
-    };
-
     int64_t c = c_begin;
     const int64_t c_sweep = c_end < maxc ? c_end : maxc;  // cycles with sweeps: [c_begin, c_sweep)
     int par = 0;        // buffer and slots of iterate c
@@ -284,7 +246,7 @@ __device__ __forceinline__ void solve_body(const Geom1 &g, const T *__restrict__
                 mine = wave_step<5>(mine);
                 k = 7;
             } else {
-                mine = finish(mine);
+                mine = wave_sum63(mine);
             }
             for (; k + 1 < s; k += 2) {
                 sweep(b, a);
@@ -328,7 +290,7 @@ __device__ __forceinline__ void solve_body(const Geom1 &g, const T *__restrict__
         // the residual of iterate maxc
         if (live) {
             load(b0 + par * pitch);
-            post(par, finish(residual()));
+            post(par, wave_sum63(residual()));
         }
         __syncthreads();
         J.take(maxc, tree_sum<SL>(red[par]));

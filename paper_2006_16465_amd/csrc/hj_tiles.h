@@ -158,15 +158,21 @@ __device__ __forceinline__ char *lds_pool()
     return pool;
 }
 
+// stop: asked once the loads are under way; true: the tile is left alone and
+// the result is negative.
+struct NeverStop {
+    __device__ bool operator()() const { return false; }
+};
+
 // One cycle of tile `tile` (row-major tile index over g's partition) by a
 // workgroup of 64 W threads.  Returns this thread's share of ||r||^2 of xin
 // over the owned points (RES), else 0.  A caller that runs several tiles in a
 // row must place a barrier between them (LDS is reused).  LB = 0: LDS arrays
 // of this instantiation; LB > 0: the lds_pool sized for LB-byte elements.
-template <typename T, int C, int R, int W, bool RES, bool ISO, bool ROT, int LB = 0>
+template <typename T, int C, int R, int W, bool RES, bool ISO, bool ROT, int LB = 0, typename Stop = NeverStop>
 __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T *__restrict__ f,
                                               const T *__restrict__ xin, T *__restrict__ xout,
-                                              int nsub)
+                                              int nsub, Stop stop = Stop{})
 {
     constexpr int TX = 16 * C, TY = 4 * R * W, NG = 4 * W;
     T(*s_top)[NG][TX];  // first row of each row group, by sweep parity
@@ -222,16 +228,19 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
         hw[i] = (j == 0 && c0 > 0) ? xin[base + (int64_t)i * ld - 1] : T(0);
         he[i] = (j == 15 && c0 + TX < g.nx) ? xin[base + (int64_t)i * ld + C] : T(0);
     }
-    if (k == 0) {
+    // frozen rows -1 (first row group) and TY (last)
+    T hrow[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            s_halo[0][lcol(c)] = r0 > 0 ? xin[(int64_t)(r0 - 1) * ld + c0 + lc0 + c] : T(0);
+    for (int c = 0; c < C; ++c) hrow[c] = T(0);
+    if (k == 0 ? r0 > 0 : (k == NG - 1 && r0 + TY < g.ny)) {
+        const T *edge = xin + (int64_t)(k == 0 ? r0 - 1 : r0 + TY) * ld + c0 + lc0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) hrow[c] = edge[c];
     }
-    if (k == NG - 1) {
+    if (stop()) return -1.0;
+    if (k == 0 || k == NG - 1) {
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            s_halo[1][lcol(c)] =
-                r0 + TY < g.ny ? xin[(int64_t)(r0 + TY) * ld + c0 + lc0 + c] : T(0);
+        for (int c = 0; c < C; ++c) s_halo[k == 0 ? 0 : 1][lcol(c)] = hrow[c];
     }
     __builtin_amdgcn_s_setprio(0);
     const int rlo = axis_own_begin(g.ny, TY, g.oy, bi) - r0 - lr0;
@@ -685,6 +694,14 @@ struct RegShape {
     static constexpr int W = TY / (4 * R);
     static constexpr bool ok = (TX == 32 || TX == 64 || TX == 128) && TY >= 16 && TY <= 128 &&
                                W >= 1 && 4 * R * W == TY;
+};
+
+// Shape for grids of few tiles: two rows a lane, so that a tile's sweep runs on
+// four times (32 x 32) or twice as many wavefronts.
+template <int TX, int TY>
+struct FewShape {
+    static constexpr int C = TX / 16, R = 2, W = TY / 8;
+    static constexpr bool ok = TX <= 64;  // interface rows of FP64 within the LDS
 };
 
 }  // namespace

@@ -18,13 +18,10 @@ __global__ __launch_bounds__((vc_threads<TX, TY>())) void k_cycle2d_vc(GeomVC g,
                                                                     Red red, double tol)
 {
     constexpr int NT = vc_threads<TX, TY>();
-    if (RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<NT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
-    const double rsq = tile_vc<TX, TY, RES>(g, xcd_tile(blockIdx.x, gridDim.x), f, xin, xout, nsub);
-    if (RES) post_partial<NT>(rsq, red.part_cur);
+    if (RES && !judged_start<NT>(red, tol)) return;
+    const int blk = judged_block<RES>();
+    const double rsq = tile_vc<TX, TY, RES>(g, xcd_tile(blk, judged_blocks<RES>()), f, xin, xout, nsub);
+    if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
 }
 
 // classical sweep (SWEEP) and / or residual (RES; with r_out when !SWEEP)
@@ -33,13 +30,11 @@ __global__ __launch_bounds__(kNT) void k_sweep2d_vc(GeomVC g, const double *__re
                                                     const double *__restrict__ xin,
                                                     double *__restrict__ xout, Red red, double tol)
 {
-    if (SWEEP && RES) {
-        if (stopped(red.ctrl, red.c)) return;
-        if (blockIdx.x == 0 && red.nb_prev > 0)
-            judge_partials<kNT>(red.part_prev, red.nb_prev, red.ctrl, red.c - 1, tol);
-    }
+    constexpr bool judged = SWEEP && RES;
+    if (judged && !judged_start<kNT>(red, tol)) return;
+    const int blk = judged_block<judged>(), nblk = judged_blocks<judged>();
     const int64_t total = (int64_t)g.nx * g.ny;
-    const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kNT + threadIdx.x;
+    const int64_t i = (int64_t)xcd_tile(blk, nblk) * kNT + threadIdx.x;
     double rsq = 0.0;
     if (i < total) {
         const int r = (int)(i / g.nx), q = (int)(i - (int64_t)r * g.nx);
@@ -57,7 +52,7 @@ __global__ __launch_bounds__(kNT) void k_sweep2d_vc(GeomVC g, const double *__re
             rsq += rr * rr;
         }
     }
-    if (RES) post_partial<kNT>(rsq, red.part_cur);
+    if (RES) post_partial<kNT>(rsq, &red.part_cur[blk]);
 }
 
 // dL/da at every node of the (ny+2) x (nx+2) grid, summed over nb right-hand
@@ -100,7 +95,7 @@ template <int TX, int TY>
 hipError_t cyc_vc(const GeomVC &g, int s, bool res, const double *f, const double *xin, double *xout,
                   const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty);
+    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
     constexpr int NT = vc_threads<TX, TY>();
     if (res) k_cycle2d_vc<TX, TY, true><<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
     else k_cycle2d_vc<TX, TY, false><<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
@@ -125,7 +120,7 @@ hipError_t launch_cycle_vc(const GeomVC &g, int s, bool res, const double *f, co
 hipError_t launch_sweep_vc(const GeomVC &g, bool res, const double *f, const double *xin, double *xout,
                            const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)sweep_vc_blocks(g);
+    const unsigned nb = (unsigned)sweep_vc_blocks(g) + (res ? 1 : 0);
     if (res) k_sweep2d_vc<true, true><<<nb, kNT, 0, st>>>(g, f, xin, xout, red, tol);
     else k_sweep2d_vc<false, true><<<nb, kNT, 0, st>>>(g, f, xin, xout, red, tol);
     return hipGetLastError();

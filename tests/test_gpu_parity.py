@@ -607,3 +607,30 @@ def test_fp32_iterates_within_1e5_of_fp64_oracle(orc):
     f1 = W.rhs_1d_modes(n, 8, 1)
     got, _ = gpu_cycles_1d(f1, np.zeros(n), 1 / (n + 1), 64, 16, 50, dtype=torch.float32)
     assert rel(got, orc.hier_1d(f1, np.zeros(n), 1 / (n + 1), 64, 16, 50)) <= 1e-5
+
+
+# ------------------------------------------------------------------ the shape for grids of few tiles
+
+@pytest.mark.parametrize("tile,n", [((32, 16), (40, 18)), ((32, 32), (33, 32)), ((32, 64), (100, 70)), ((32, 128), (64, 129)),
+                                    ((64, 16), (64, 16)), ((64, 32), (70, 65)), ((64, 64), (129, 64)), ((64, 128), (64, 130)),
+                                    ((32, 32), (1024, 1024)), ((32, 32), (1056, 1024))])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("iso", [True, False])
+def test_few_tiles_shape_matches_oracle(orc, tile, n, dtype, iso):
+    """Grids of one to a few tiles run two rows a lane, with their own order of
+    loads and flag; 1024^2 and 1056 x 1024 with 32 x 32 tiles lie on either
+    side of the rule.  Cycles that fuse the residual, and cycles that do not."""
+    nx, ny = n
+    f, x0 = W.rhs_random((ny, nx), 21), W.rhs_random((ny, nx), 22)
+    hx = 1.0 / (nx + 1)
+    hy = hx if iso else 1.3 * hx
+    hier = orc.hier_2d if dtype == torch.float64 else orc.hier_2d_f32
+    for s, ov, nc in ((1, (0, 0), 3), (4, (6, 6), 2), (5, (3, 2), 3)):
+        say(f"few tiles {tile} {n} {dtype} iso={iso} s={s}")
+        want = hier(f, x0, hx, hy, tile, s, nc, ov)
+        for tol in (0.0, 1e-100):
+            F, X = dev(f, dtype), dev(x0, dtype)
+            info = hj.solve_2d(F, X, hx=hx, hy=hy, tile=tile, s=s, overlap=ov, rel_tol=tol, max_cycles=nc,
+                               allow_not_converged=True)
+            assert info.cycles == nc
+            assert np.array_equal(host(X), want), (s, ov, tol)
