@@ -82,13 +82,11 @@ def sweep_bytes_per_launch(n, esize=8):
 
 def cycle_kernel_name(tile, n):
     """Name of the cycle kernel the library runs for this tile on an n x n
-    grid: register-resident tiles of C = tx/16 columns and R rows per lane over
-    W wavefronts (R = ty/4 up to 64 x 32; 4 rows, 8 at tx = 32, above), else
-    the LDS kernel."""
+    grid of many tiles: register-resident tiles of C = tx/16 columns and 4 rows
+    per lane over W wavefronts, else the LDS kernel."""
     tx, ty = tile
     if tx in (32, 64, 128) and ty in (16, 32, 64, 128) and n >= max(tile):
-        r = ty // 4 if (tx <= 64 and ty <= 32) else (8 if tx == 32 else 4)
-        return f"k_cycle2d_reg<double,{tx // 16},{r},{ty // (4 * r)},true,true>"
+        return f"k_cycle2d_reg<double,{tx // 16},4,{ty // 16},true,true,false>"
     return f"k_cycle2d<double,{tx},{ty},true,true>"
 
 
@@ -106,8 +104,7 @@ def cycle_lds_bytes_per_launch(n, tile, overlap, s, esize=8):
     if not cycle_kernel_name(tile, n).startswith("k_cycle2d_reg"):
         return None
     c = tx // 16
-    r = ty // 4 if (tx <= 64 and ty <= 32) else (8 if tx == 32 else 4)
-    threads = 64 * (ty // (4 * r))
+    threads = 64 * (ty // 16)
     tiles = hj.axis_tiles(n, tx, overlap[0]) * hj.axis_tiles(n, ty, overlap[1])
     return tiles * threads * s * 4 * c * esize
 

@@ -338,6 +338,7 @@ hj::Geom2 make_geom2(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, c
     g.oy = p.overlap_y;
     g.ntx = hj::axis_count(g.nx, g.tx, g.ox);
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
+    g.walk = hj::make_walk(g.ntx, g.nty, 24 * (int64_t)g.tx * g.ty);
     g.iso = hx == hy;
     g.reg = (p.flags & HJ_FLAG_LDS_KERNEL) ? 0 : 1;
     g.hh = hx * hx;
@@ -388,6 +389,7 @@ hj::GeomVC make_geom_vc(const hj_vc_problem &pr, const hj_params &p)
     g.oy = p.overlap_y;
     g.ntx = hj::axis_count(g.nx, g.tx, g.ox);
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
+    g.walk = hj::make_walk(g.ntx, g.nty, 32 * (int64_t)g.tx * g.ty);
     g.a = pr.a;
     g.lda = pr.lda;
     g.ihx2 = 1.0 / (pr.hx * pr.hx);

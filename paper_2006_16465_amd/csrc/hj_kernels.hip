@@ -42,7 +42,8 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
     __shared__ T buf[2][R * P];
 
     const int tile = xcd_tile(blk, nblk);
-    const int bi = tile / g.ntx, bj = tile - bi * g.ntx;
+    int bi, bj;
+    tile_pos(g.walk, tile, bi, bj);
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
     const int c0 = axis_origin(g.nx, TX, g.ox, bj);
     const int ey = g.ny < TY ? g.ny : TY;
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(64 * W, (min_waves_2d<T, C, R>())) void k_cycle2d_r
     const int blk = judged_block<RES>();
     const int tile = xcd_tile(blk, judged_blocks<RES>());
     auto stop = [&] { return RES && FEW && stopped(red.ctrl, red.c); };
-    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, !FEW && rotate_rows<T>(), 0>(g, tile, f, xin, xout, nsub, stop);
+    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, 0>(g, tile, f, xin, xout, nsub, stop);
     if (RES && FEW && rsq < 0.0) return;
     if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
 }
@@ -266,9 +267,10 @@ constexpr bool lds_shape(int tx, int ty)
 // The FEW shape is taken where the tiles of the ordinary one have no more
 // wavefronts than the chip has SIMDs (4 on each of 256 CUs): each then runs
 // alone on its SIMD and a sweep takes as long as its own chain.  Measured, us
-// per FP64 cycle, ordinary / FEW shape: 32 x 32 tiles at s = 16, 512^2 (256
-// wavefronts) 8.3 / 5.8, 1024^2 (1 024) 10.9 / 9.8, 4096^2 (16 384) 90 / 98;
-// 64 x 64 at s = 10, 512^2 (484) 8.5 / 8.3, 1024^2 (1 936) 12.0 / 12.3.
+// per FP64 cycle, ordinary / FEW shape: 32 x 32 tiles at s = 16, 512^2 (512
+// wavefronts) 6.9 / 5.8, 4096^2 (32 768) 90 / 98; 64 x 64 at s = 10, 512^2
+// (484) 8.5 / 8.3, 1024^2 (1 936) 12.0 / 12.3; 32 x 64 at s = 32, 1024^2
+// (3 268) 19.3 / 23.6.
 constexpr int64_t kSimds = 1024;
 
 template <typename T, int C, int R, int W, bool FEW>

@@ -16,6 +16,7 @@ struct Geom2 {
     int64_t ld;
     int tx, ty, ox, oy;  // tile extents and overlaps
     int ntx, nty;        // tiles per axis
+    Walk walk;           // order of the tiles
     int iso;             // hx == hy: use the h^2 f form of the update
     int reg;             // allow the register-resident cycle kernel (full tiles only)
     double hh;           // h^2 (iso)
@@ -96,6 +97,7 @@ struct GeomVC {
     int nx, ny;
     int64_t ld;
     int tx, ty, ox, oy, ntx, nty;
+    Walk walk;
     const double *a;  // (ny+2) x lda node coefficients
     int64_t lda;
     double ihx2, ihy2;

@@ -14,17 +14,6 @@
 namespace hj {
 namespace {
 
-// Rows in R + 1 rotating register slots (no register moves, straight-line
-// rounds of R + 1 sweeps) or updated in place (one move per point and sweep).
-// Measured at 4096^2: rotation costs FP64 about 34 VGPRs and one wave per
-// SIMD (64x128: 236 against 183 us per cycle) but saves FP32 about a tenth
-// (89 against 98 us), where the registers are half the size.
-template <typename T>
-constexpr bool rotate_rows()
-{
-    return sizeof(T) == 4;
-}
-
 // ---------------------------------------------------------------- updates
 // 2D: iso  -> (h^2 f + ((W + E) + (S + N))) * 0.25      (Sec. 4.2, dx == dy)
 //     else -> (f + (wx (W + E) + wy (S + N))) * dinv    (Sec. 4.2 general form)
@@ -42,28 +31,26 @@ __device__ __forceinline__ T upd1(T bh, T w, T e)
     return (bh + (w + e)) * T(0.5);
 }
 
-// r = f - A x in FP64
+// r = f - A x in FP64.  2 x - w is written as one FMA: 2 x is exact, so the
+// difference is rounded once either way.
 __device__ __forceinline__ double res2(double f, double x, double w, double e, double s, double n,
                                        double wx, double wy)
 {
-    return f - (wx * ((2.0 * x - w) - e) + wy * ((2.0 * x - s) - n));
+    return f - (wx * (__builtin_fma(2.0, x, -w) - e) + wy * (__builtin_fma(2.0, x, -s) - n));
 }
 
 __device__ __forceinline__ double res1(double f, double x, double w, double e, double w1)
 {
-    return f - w1 * ((2.0 * x - w) - e);
+    return f - w1 * (__builtin_fma(2.0, x, -w) - e);
 }
 
 constexpr int kNT = 256;  // threads per workgroup of every kernel here
 
 // Minimum wavefronts per SIMD the 2D register-tile kernels ask the compiler
-// for (the second __launch_bounds__ argument).  FP64 tiles of 4 x 4 points a
-// lane (64x64, 64x128) hold 124 VGPRs with a rolled sweep loop and 132 with
-// the unrolled one: capped at 128 (occupancy 4) the compiler spills one
-// double outside the loop, and the launch beats the rolled loop (4096^2,
-// s = 16: 147-150 against 153-158 us); left at 132 VGPRs (occupancy 3) an
-// s = 12 launch took over 200 us against 135.  Other shapes need more
-// registers than 4 waves allow and are left to the compiler.
+// for (the second __launch_bounds__ argument): FP64 tiles of 4 x 4 points a
+// lane fit 128 VGPRs (occupancy 4) without a spill, which the compiler finds
+// only when it is asked to; at occupancy 3 an s = 12 launch at 4096^2 took over
+// 200 us against 135.  Other shapes are left to the compiler.
 template <typename T, int C, int R>
 constexpr int min_waves_2d()
 {
@@ -148,6 +135,10 @@ __device__ __forceinline__ float fma_quarter(float sv, float b)
     return r;
 }
 
+// v is formed here (and not where its use lies, with all it is formed from
+// kept in registers until then)
+__device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }
+
 // LDS of BYTES bytes; every caller asking for the same size gets the same
 // array, so a kernel that runs reg_tile_2d in two precisions (never both in
 // one workgroup) can size it for the wider one and hold it once.
@@ -158,18 +149,33 @@ __device__ __forceinline__ char *lds_pool()
     return pool;
 }
 
+// The owned part [clo, chi) of a lane's run of C columns.  Lanes that own the
+// whole run store it in 16-byte pieces; stored point by point a wavefront sent
+// every 128-byte line to L2 in four pieces.
+template <typename T, int C>
+__device__ __forceinline__ void store_run(T *p, const T (&v)[C], int clo, int chi)
+{
+    if (clo <= 0 && chi >= C) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) p[c] = v[c];
+    } else if (chi > 0 && clo < C) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (c >= clo && c < chi) p[c] = v[c];
+    }
+}
+
 // stop: asked once the loads are under way; true: the tile is left alone and
 // the result is negative.
 struct NeverStop {
     __device__ bool operator()() const { return false; }
 };
 
-// One cycle of tile `tile` (row-major tile index over g's partition) by a
-// workgroup of 64 W threads.  Returns this thread's share of ||r||^2 of xin
+// One cycle of tile `tile` of g's walk by a workgroup of 64 W threads.  Returns this thread's share of ||r||^2 of xin
 // over the owned points (RES), else 0.  A caller that runs several tiles in a
 // row must place a barrier between them (LDS is reused).  LB = 0: LDS arrays
 // of this instantiation; LB > 0: the lds_pool sized for LB-byte elements.
-template <typename T, int C, int R, int W, bool RES, bool ISO, bool ROT, int LB = 0, typename Stop = NeverStop>
+template <typename T, int C, int R, int W, bool RES, bool ISO, int LB = 0, typename Stop = NeverStop>
 __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T *__restrict__ f,
                                               const T *__restrict__ xin, T *__restrict__ xout,
                                               int nsub, Stop stop = Stop{})
@@ -194,7 +200,8 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
     }
 
     const int k = (int)threadIdx.x >> 4, j = (int)threadIdx.x & 15;
-    const int bi = tile / g.ntx, bj = tile - bi * g.ntx;
+    int bi, bj;
+    tile_pos(g.walk, tile, bi, bj);
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
     const int c0 = axis_origin(g.nx, TX, g.ox, bj);
     const int64_t ld = g.ld;
@@ -210,14 +217,13 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
         else return j * C + c;
     };
 
-    // step 1: tile, halo and f into registers / LDS (phase 0: row i in slot i).
+    // step 1: tile, halo and f into registers / LDS.
     // The loads issue at raised wave priority, the sweeps at the base one:
     // the workgroup that is loading gets its memory instructions out ahead
     // of the sweeping workgroup's VALU work on the same SIMDs, so the two
     // phases overlap better (4 % per 4096^2 cycle, measured A/B).
     __builtin_amdgcn_s_setprio(3);
-    constexpr int NS = ROT ? R + 1 : R;
-    T x[NS][C], bq[R][C], hw[R], he[R];
+    T x[R][C], bq[R][C], hw[R], he[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
 #pragma unroll
@@ -225,6 +231,10 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
             x[i][c] = xin[base + (int64_t)i * ld + c];
             bq[i][c] = f[base + (int64_t)i * ld + c];  // f for now, scaled after the residual
         }
+        // frozen columns: -1 in the first lane of a row group, TX in its last
+        // (the other lanes' values are not used).  Row by row among the
+        // tile's loads: one masked block after them all was slower (FP32 64 x
+        // 64 s = 12 at 4096^2 64.6 against 60.7 us without residual).
         hw[i] = (j == 0 && c0 > 0) ? xin[base + (int64_t)i * ld - 1] : T(0);
         he[i] = (j == 15 && c0 + TX < g.nx) ? xin[base + (int64_t)i * ld + C] : T(0);
     }
@@ -243,10 +253,11 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
         for (int c = 0; c < C; ++c) s_halo[k == 0 ? 0 : 1][lcol(c)] = hrow[c];
     }
     __builtin_amdgcn_s_setprio(0);
-    const int rlo = axis_own_begin(g.ny, TY, g.oy, bi) - r0 - lr0;
-    const int rhi = axis_own_end(g.ny, TY, g.oy, bi, g.nty) - r0 - lr0;
-    const int clo = axis_own_begin(g.nx, TX, g.ox, bj) - c0 - lc0;
-    const int chi = axis_own_end(g.nx, TX, g.ox, bj, g.ntx) - c0 - lc0;
+    // owned rows and columns of the tile (uniform)
+    const int orlo = axis_own_begin(g.ny, TY, g.oy, bi) - r0;
+    const int orhi = axis_own_end(g.ny, TY, g.oy, bi, g.nty) - r0;
+    const int oclo = axis_own_begin(g.nx, TX, g.ox, bj) - c0;
+    const int ochi = axis_own_end(g.nx, TX, g.ox, bj, g.ntx) - c0;
 
     const T wx = T(g.wx), wy = T(g.wy), dinv = T(g.dinv);
     T up[C], dn[C];
@@ -254,11 +265,11 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
     // fetch the neighbouring groups' (or the frozen halo rows).  A buffer is
     // rewritten two sweeps later, after a barrier that every thread reaches
     // only once its reads from it are done.
-    auto exchange = [&]<int P>(int par) {
+    auto exchange = [&](int par) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            s_top[par][k][lcol(c)] = x[P % NS][c];
-            s_bot[par][k][lcol(c)] = x[(R - 1 + P) % NS][c];
+            s_top[par][k][lcol(c)] = x[0][c];
+            s_bot[par][k][lcol(c)] = x[R - 1][c];
         }
         __syncthreads();
         const T *pu = k == 0 ? s_halo[0] : s_bot[par][k - 1];
@@ -270,94 +281,31 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
         }
     };
 
-    double rsq = 0.0;
-    const T hh = T(g.hh);
-    if constexpr (ROT) {
-    // One sub-iteration at phase P: row i of the lane sits in slot (i + P) mod NS
-    // and its new value goes to the slot of row i - 1 (free once new row i is
-    // formed; for row 0 the spare slot), so the sweep leaves phase P - 1 and
-    // moves no registers.  FIRST: bq still holds f; it also accumulates the
-    // residual of the incoming iterate over the owned points and scales f
-    // (h^2 f / 4 when isotropic) as it goes.
-    auto sweep = [&]<int P, bool FIRST>() {
-        T above[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) above[c] = up[c];
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int cur = (i + P) % NS;
-            const int dst = (i + P + NS - 1) % NS;
-            const T wl = dpp_shift<kDppRowShr1>(x[cur][C - 1]);
-            const T er = dpp_shift<kDppRowShl1>(x[cur][0]);
-            T nw[C];
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const T w = c > 0 ? x[cur][c - 1] : wl;
-                const T e = c < C - 1 ? x[cur][c + 1] : er;
-                T we = w + e;
-                // the halo registers are 0 except in the first / last lane of a
-                // DPP row, where the shifted value is 0: the sum stays W + E
-                if (c == 0) we = we + hw[i];
-                if (c == C - 1) we = we + he[i];
-                const T below = i < R - 1 ? x[(i + 1 + P) % NS][c] : dn[c];
-                const T sn = above[c] + below;
-                if (FIRST) {
-                    if (RES && i >= rlo && i < rhi && c >= clo && c < chi) {
-                        const double wa = c > 0 ? (double)w : (double)wl + (double)hw[i];
-                        const double ea = c < C - 1 ? (double)e : (double)er + (double)he[i];
-                        const double rr = res2((double)bq[i][c], (double)x[cur][c], wa, ea,
-                                               (double)above[c], (double)below, g.wx, g.wy);
-                        rsq += rr * rr;
-                    }
-                    if (ISO) bq[i][c] = (hh * bq[i][c]) * T(0.25);
-                }
-                if (ISO) nw[c] = fma_quarter(we + sn, bq[i][c]);
-                else nw[c] = (bq[i][c] + (wx * we + wy * sn)) * dinv;
-            }
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                above[c] = x[cur][c];
-                x[dst][c] = nw[c];
-            }
+    // Residual over the owned points.  FP32 64 x 128 tiles form every point by
+    // itself, masked, from opaque copies: that keeps the FP64 values of its
+    // neighbours from living on, so the kernel holds 80 VGPRs and three
+    // workgroups fit a compute unit instead of two (4096^2, s = 12, us per
+    // cycle: 74 -> 64; elsewhere the masked block per point is up to 5 %
+    // faster, as lanes that own nothing skip it).
+    constexpr bool NARROW = sizeof(T) == 4 && C == 4 && R == 4 && W == 8;
+    double rsq = 0.0, racc = 0.0;
+    const int rlo = orlo - lr0, rhi = orhi - lr0, clo = oclo - lc0, chi = ochi - lc0;
+    auto residual = [&](int i, int c, T fv, T xv, double w, double e, T s, T n) {
+        if constexpr (NARROW) {
+            asm volatile("" : "+v"(s), "+v"(n));
+            double rr = res2((double)fv, (double)xv, w, e, (double)s, (double)n, g.wx, g.wy);
+            rr = c >= clo && c < chi ? rr : 0.0;
+            racc = __builtin_fma(rr, rr, c == 0 ? 0.0 : racc);
+            pin(racc);
+            __builtin_amdgcn_sched_barrier(0);
+            if (c == C - 1) rsq = i >= rlo && i < rhi ? rsq + racc : rsq;
+        } else if (i >= rlo && i < rhi && c >= clo && c < chi) {
+            const double rr = res2((double)fv, (double)xv, w, e, (double)s, (double)n, g.wx, g.wy);
+            rsq = __builtin_fma(rr, rr, rsq);
         }
     };
-    auto step = [&]<int P>(int it) {
-        exchange.template operator()<P>(it & 1);
-        sweep.template operator()<P, false>();
-    };
-
-    // step 2: nsub sub-iterations with the halo frozen.  The first runs at
-    // phase 0 and leaves phase NS - 1; full rounds of NS sweeps (phases
-    // NS - 1 .. 0, straight-line code) return there; each remainder sweep
-    // lowers the phase by one.
-    exchange.template operator()<0>(0);
-    sweep.template operator()<0, true>();
-    int it = 1;
-    for (; it + NS <= nsub; it += NS) {
-        [&]<int... Ps>(std::integer_sequence<int, Ps...>) {
-            (step.template operator()<NS - 1 - Ps>(it + Ps), ...);
-        }(std::make_integer_sequence<int, NS>{});
-    }
-    const int rem = nsub - it;  // 0 <= rem < NS
-    [&]<int... Ps>(std::integer_sequence<int, Ps...>) {
-        ((rem > Ps ? (step.template operator()<NS - 1 - Ps>(it + Ps), 0) : 0), ...);
-    }(std::make_integer_sequence<int, NS - 1>{});
-    const int ph = NS - 1 - rem;
-
-    // step 3: owned points back to global memory (row i in slot (i + ph) mod NS)
-    [&]<int... Ps>(std::integer_sequence<int, Ps...>) {
-        ((ph == Ps ? ([&] {
-#pragma unroll
-              for (int i = 0; i < R; ++i)
-#pragma unroll
-                  for (int c = 0; c < C; ++c)
-                      if (i >= rlo && i < rhi && c >= clo && c < chi)
-                          xout[base + (int64_t)i * ld + c] = x[(i + Ps) % NS][c];
-          }(), 0) : 0),
-         ...);
-    }(std::make_integer_sequence<int, NS>{});
-
-    } else {
+    // h^2 f / 4 with one rounding (the power of two commutes with it)
+    const T hq = T(g.hh) * T(0.25);
     // One sub-iteration over the lane's rows, top to bottom, in place: prev
     // keeps the old row above.  FIRST: bq still holds f; it also accumulates
     // the residual of the incoming iterate over the owned points and scales f
@@ -382,12 +330,8 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
                 const T below = i < R - 1 ? x[i + 1][c] : dn[c];
                 const T sn = prev[c] + below;
                 if (FIRST) {
-                    if (RES && i >= rlo && i < rhi && c >= clo && c < chi) {
-                        const double rr = res2((double)bq[i][c], (double)x[i][c], (double)w, (double)e,
-                                               (double)prev[c], (double)below, g.wx, g.wy);
-                        rsq += rr * rr;
-                    }
-                    if (ISO) bq[i][c] = (hh * bq[i][c]) * T(0.25);
+                    if (RES) residual(i, c, bq[i][c], x[i][c], (double)w, (double)e, prev[c], below);
+                    if (ISO) bq[i][c] = hq * bq[i][c];
                 }
                 if (ISO) nw[c] = fma_quarter(we + sn, bq[i][c]);
                 else nw[c] = (bq[i][c] + (wx * we + wy * sn)) * dinv;
@@ -397,6 +341,7 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
                 prev[c] = x[i][c];
                 x[i][c] = nw[c];
             }
+            if (FIRST && RES) pin(rsq);
         }
     };
 
@@ -404,30 +349,32 @@ __device__ __forceinline__ double reg_tile_2d(const Geom2 &g, int tile, const T 
     // each exchange's LDS buffer is then a constant, and the two sweeps
     // trade the rows' registers between them, so the loop carries no address
     // arithmetic and no register moves (80 VALU instructions per sweep and
-    // wavefront against 104 at 4 x 4 points a lane); it takes a few more
-    // VGPRs, which the kernels cap (min_waves_2d) to keep occupancy 4.
-    exchange.template operator()<0>(0);
+    // wavefront against 104 at 4 x 4 points a lane).
+    exchange(0);
     sweep(std::true_type{});
     int it = 1;
     for (; it + 1 < nsub; it += 2) {
-        exchange.template operator()<0>(1);
+        exchange(1);
         sweep(std::false_type{});
-        exchange.template operator()<0>(0);
+        exchange(0);
         sweep(std::false_type{});
     }
     if (it < nsub) {
-        exchange.template operator()<0>(1);
+        exchange(1);
         sweep(std::false_type{});
     }
 
-    // step 3: owned points back to global memory
+    // step 3: owned points back to global memory.  The lane's place is formed
+    // again from its index: kept from the load it held registers through the
+    // sweeps, and the FP64 kernels spilled 2 to 5 (4096^2, us per cycle: 64 x
+    // 64 s = 12 149 -> 133, 64 x 128 s = 16 147 -> 140).
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int wr = (tid >> 4) * R, wc = (tid & 15) * C;
+    T *out = xout + (int64_t)(r0 + wr) * ld + c0 + wc;
 #pragma unroll
     for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            if (i >= rlo && i < rhi && c >= clo && c < chi) xout[base + (int64_t)i * ld + c] = x[i][c];
-
-    }
+        if (i >= orlo - wr && i < orhi - wr) store_run<T, C>(out + (int64_t)i * ld, x[i], oclo - wc, ochi - wc);
     return rsq;
 }
 
@@ -683,21 +630,24 @@ __device__ __forceinline__ double tiles_1d(const Geom1 &g, int64_t blk, const T 
 }
 
 
-// Register-resident shape for a TX x TY tile: C columns and R rows per lane,
-// W wavefronts.  Up to 32 x 32 one wavefront holds the tile (R = TY / 4);
-// taller tiles use 4 rows per lane (8 at TX = 32) and more wavefronts, which
-// keeps the per-lane footprint small enough for three or more waves per SIMD.
+// Register-resident shape for a TX x TY tile: C columns and R = 4 rows per
+// lane, W wavefronts.  Eight rows a lane (32 x 32 and 64 x 32 on one
+// wavefront, 32 x 64 on two) move half the interface rows but hold twice the
+// registers: us per cycle, eight rows / four, FP64 1024^2 64 x 32 s = 8 o = 14
+// 14.3 / 12.4, 32 x 64 s = 32 o = 8 21.3 / 19.3, FP32 2048^2 32 x 64 41.7 /
+// 36.9; equal within 2 % for 32 x 32 on larger grids, 124 / 130 at worst
+// (FP64 4096^2 64 x 32).
 template <int TX, int TY>
 struct RegShape {
     static constexpr int C = TX / 16;
-    static constexpr int R = (TX <= 64 && TY <= 32) ? TY / 4 : (TX == 32 ? 8 : 4);
+    static constexpr int R = 4;
     static constexpr int W = TY / (4 * R);
     static constexpr bool ok = (TX == 32 || TX == 64 || TX == 128) && TY >= 16 && TY <= 128 &&
                                W >= 1 && 4 * R * W == TY;
 };
 
 // Shape for grids of few tiles: two rows a lane, so that a tile's sweep runs on
-// four times (32 x 32) or twice as many wavefronts.
+// twice as many wavefronts.
 template <int TX, int TY>
 struct FewShape {
     static constexpr int C = TX / 16, R = 2, W = TY / 8;

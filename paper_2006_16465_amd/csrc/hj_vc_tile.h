@@ -79,7 +79,8 @@ __device__ __forceinline__ double lds_tile_vc(const GeomVC &g, int tile, const d
     constexpr int P = TX + 2, R = TY + 2, PER = TX * TY / NT, RSTEP = NT / TX;
     double(*buf)[R * P] = reinterpret_cast<double(*)[R * P]>(pool);
 
-    const int bi = tile / g.ntx, bj = tile - bi * g.ntx;
+    int bi, bj;
+    tile_pos(g.walk, tile, bi, bj);
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
     const int c0 = axis_origin(g.nx, TX, g.ox, bj);
     const int ey = g.ny < TY ? g.ny : TY;
@@ -179,7 +180,8 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
     double(*s_halo)[TX] = reinterpret_cast<double(*)[TX]>(pool + 4 * NG * TX * 8);
 
     const int k = (int)threadIdx.x >> 4, j = (int)threadIdx.x & 15;
-    const int bi = tile / g.ntx, bj = tile - bi * g.ntx;
+    int bi, bj;
+    tile_pos(g.walk, tile, bi, bj);
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
     const int c0 = axis_origin(g.nx, TX, g.ox, bj);
     const int64_t ld = g.ld;

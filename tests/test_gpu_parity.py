@@ -634,3 +634,14 @@ def test_few_tiles_shape_matches_oracle(orc, tile, n, dtype, iso):
                                allow_not_converged=True)
             assert info.cycles == nc
             assert np.array_equal(host(X), want), (s, ov, tol)
+
+
+@pytest.mark.parametrize("n,tile,ov", [((5003, 3301), (32, 32), (6, 2)), ((2600, 6007), (64, 128), (22, 22))])
+def test_strip_walk_reaches_every_tile(orc, n, tile, ov):
+    """Grids large enough to be walked in strips, ragged, the last strip narrower than the others."""
+    nx, ny = n
+    f, x0 = W.rhs_random((ny, nx), 31), W.rhs_random((ny, nx), 32)
+    h = 1.0 / (nx + 1)
+    say(f"strip walk {n} {tile} {ov}")
+    got, _ = gpu_cycles_2d(f, x0, h, tile, 2, 2, ov)
+    assert np.array_equal(got, orc.hier_2d(f, x0, h, h, tile, 2, 2, ov))
