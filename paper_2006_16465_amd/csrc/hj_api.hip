@@ -795,7 +795,7 @@ hj_status run_batch(const hj_problem *probs, int64_t nprob, hj_dtype dt, double 
             if (ce == hipSuccess) ce = hj::launch_batch_cycle2d(idt, refine, P2.tile_x, P2.tile_y, true, Li, B.cap);
             if (ce == hipSuccess) ce = hj::launch_batch_cycle2d(idt, refine, P2.tile_x, P2.tile_y, false, Lg, B.cap);
             if (ce == hipSuccess) ce = hj::launch_batch_cycle1d(idt, refine, P1.tile_x, L1, B.cap);
-            if (ce == hipSuccess) ce = hj::launch_batch_cycle_vc(P2.tile_x, P2.tile_y, Lv, B.cap);
+            if (ce == hipSuccess && vc) ce = hj::launch_batch_cycle_vc(*vc, Lv, B.cap);
             if (ce == hipSuccess) ce = hj::launch_batch_judge(B.probs, (int)nprob, B.state, B.part, rf, B.cap);
         }
         const hipError_t ee = hipStreamEndCapture(B.cap, &graph);

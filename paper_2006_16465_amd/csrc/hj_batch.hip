@@ -172,8 +172,8 @@ __global__ __launch_bounds__(kNT) void k_batch_cycle1d(const BProb *__restrict__
 
 // Variable-coefficient 2D problems (dim 3, FP64, plain): the tile bodies of
 // the single-problem kernel (hj_vc_tile.h).
-template <int TX, int TY>
-__global__ __launch_bounds__((vc_threads<TX, TY>())) void k_batch_cycle_vc(const BProb *__restrict__ probs,
+template <int TX, int TY, bool REG>
+__global__ __launch_bounds__((vc_threads<TX, TY>()), (vc_min_waves<TX, REG>())) void k_batch_cycle_vc(const BProb *__restrict__ probs,
                                                         const int32_t *__restrict__ owner, int64_t nitems,
                                                         const BState *__restrict__ state, double *part, int s)
 {
@@ -187,7 +187,7 @@ __global__ __launch_bounds__((vc_threads<TX, TY>())) void k_batch_cycle_vc(const
     double *xout;
     main_arrays<double>(P, S, xin, xout);
     const int tile = (int)(w - P.item0);
-    const double rsq = tile_vc<TX, TY, true>(P.gv, tile, (const double *)P.f, xin, xout, s);
+    const double rsq = tile_vc<TX, TY, true, REG>(P.gv, tile, (const double *)P.f, xin, xout, s);
     post_partial<vc_threads<TX, TY>()>(rsq, &part[P.part0 + tile]);
 }
 
@@ -511,10 +511,10 @@ hipError_t bcyc1_m(int t, const BatchLaunch &L, hipStream_t st)
     }
 }
 
-template <int TX, int TY>
+template <int TX, int TY, bool REG>
 hipError_t bcycvc(const BatchLaunch &L, hipStream_t st)
 {
-    k_batch_cycle_vc<TX, TY><<<(unsigned)L.nitems, vc_threads<TX, TY>(), 0, st>>>(L.probs, L.owner, L.nitems,
+    k_batch_cycle_vc<TX, TY, REG><<<(unsigned)L.nitems, vc_threads<TX, TY>(), 0, st>>>(L.probs, L.owner, L.nitems,
                                                                                   L.state, L.part, L.s);
     return hipGetLastError();
 }
@@ -530,11 +530,12 @@ bool batch_vc_supported(int tx, int ty)
     return false;
 }
 
-hipError_t launch_batch_cycle_vc(int tx, int ty, const BatchLaunch &L, hipStream_t st)
+hipError_t launch_batch_cycle_vc(const GeomVC &g, const BatchLaunch &L, hipStream_t st)
 {
     if (L.nitems <= 0) return hipSuccess;
+    const bool reg = vc_reg(g);
 #define HJ_TILE(a, b) \
-    if (tx == a && ty == b) return bcycvc<a, b>(L, st);
+    if (g.tx == a && g.ty == b) return reg ? bcycvc<a, b, true>(L, st) : bcycvc<a, b, false>(L, st);
     HJ_VC_TILES(HJ_TILE)
 #undef HJ_TILE
     return hipErrorInvalidValue;

@@ -197,7 +197,8 @@ hipError_t launch_batch_cycle2d(int dt, bool refine, int tx, int ty, bool iso, c
                                 hipStream_t st);
 hipError_t launch_batch_cycle1d(int dt, bool refine, int t, const BatchLaunch &L, hipStream_t st);
 bool batch_vc_supported(int tx, int ty);
-hipError_t launch_batch_cycle_vc(int tx, int ty, const BatchLaunch &L, hipStream_t st);
+// g: the operator that all variable-coefficient problems of the batch share
+hipError_t launch_batch_cycle_vc(const GeomVC &g, const BatchLaunch &L, hipStream_t st);
 hipError_t launch_batch_judge(const BProb *probs, int nprob, BState *state, const double *part,
                               const BRefine &rf, hipStream_t st);
 hipError_t launch_batch_init(BState *state, int nprob, hipStream_t st);

@@ -11,8 +11,8 @@
 namespace hj {
 namespace {
 
-template <int TX, int TY, bool RES>
-__global__ __launch_bounds__((vc_threads<TX, TY>())) void k_cycle2d_vc(GeomVC g, const double *__restrict__ f,
+template <int TX, int TY, bool RES, bool REG>
+__global__ __launch_bounds__((vc_threads<TX, TY>()), (vc_min_waves<TX, REG>())) void k_cycle2d_vc(GeomVC g, const double *__restrict__ f,
                                                                     const double *__restrict__ xin,
                                                                     double *__restrict__ xout, int nsub,
                                                                     Red red, double tol)
@@ -20,7 +20,7 @@ __global__ __launch_bounds__((vc_threads<TX, TY>())) void k_cycle2d_vc(GeomVC g,
     constexpr int NT = vc_threads<TX, TY>();
     if (RES && !judged_start<NT>(red, tol)) return;
     const int blk = judged_block<RES>();
-    const double rsq = tile_vc<TX, TY, RES>(g, xcd_tile(blk, judged_blocks<RES>()), f, xin, xout, nsub);
+    const double rsq = tile_vc<TX, TY, RES, REG>(g, xcd_tile(blk, judged_blocks<RES>()), f, xin, xout, nsub);
     if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
 }
 
@@ -97,9 +97,12 @@ hipError_t cyc_vc(const GeomVC &g, int s, bool res, const double *f, const doubl
 {
     const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
     constexpr int NT = vc_threads<TX, TY>();
-    if (res) k_cycle2d_vc<TX, TY, true><<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
-    else k_cycle2d_vc<TX, TY, false><<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        kernel<<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
+        return hipGetLastError();
+    };
+    if (vc_reg(g)) return res ? go(k_cycle2d_vc<TX, TY, true, true>) : go(k_cycle2d_vc<TX, TY, false, true>);
+    return res ? go(k_cycle2d_vc<TX, TY, true, false>) : go(k_cycle2d_vc<TX, TY, false, false>);
 }
 
 }  // namespace

@@ -40,7 +40,7 @@ __device__ __forceinline__ Face face_at(const GeomVC &g, int r, int q)
 // Workgroup shape of the variable-coefficient cycle on a TX x TY tile: W
 // wavefronts of 16-lane row groups, each lane holding C = TX / 16 columns of
 // R = 2 rows (TY = 4 R W).  Both tile bodies below run with these 64 W
-// threads, so one kernel can hold both.
+// threads.
 template <int TX, int TY>
 struct VcShape {
     static constexpr int C = TX / 16, R = 2, W = TY / (4 * R), NT = 64 * W;
@@ -53,13 +53,11 @@ __host__ __device__ constexpr int vc_threads()
     return VcShape<TX, TY>::NT;
 }
 
-// LDS bytes either body needs (one pool serves both)
-template <int TX, int TY>
+// LDS bytes of a body
+template <int TX, int TY, bool REG>
 constexpr int vc_lds_bytes()
 {
-    constexpr int lds = 2 * (TX + 2) * (TY + 2) * 8;
-    constexpr int reg = (4 * 4 * VcShape<TX, TY>::W * TX + 2 * TX) * 8;
-    return lds > reg ? lds : reg;
+    return REG ? (4 * 4 * VcShape<TX, TY>::W * TX + 2 * TX) * 8 : 2 * (TX + 2) * (TY + 2) * 8;
 }
 
 // LDS ping-pong body, any grid (also smaller than a tile).
@@ -194,31 +192,43 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
     };
 
     // step 1: x, f, the x-halo and the face weights into registers, the
-    // frozen halo rows into LDS.  ab[ii * lda + cc] is the node of interior
-    // point (r0 + lr0 + ii - 1, c0 + lc0 + cc - 1).
+    // frozen halo rows into LDS.  Row ii of A holds the nodes of points
+    // (r0 + lr0 + ii - 1, c0 + lc0 + c); the node columns beside the lane's
+    // come from the lanes beside it (aw, ae: the row group's ends load theirs),
+    // so a node row is read once per row group in 16-byte pieces.
     double x[R][C], fv[R][C], fe[R][C], fn[R][C], di[R][C], fw0[R], fs0[C], hw[R], he[R];
     {
-        const double *ab = g.a + (int64_t)(r0 + lr0) * g.lda + (c0 + lc0);
-        double A[R + 2][C + 2];
+        const double *ab = g.a + (int64_t)(r0 + lr0) * g.lda + (c0 + lc0 + 1);
+        double A[R + 2][C], aw[R], ae[R];
 #pragma unroll
         for (int ii = 0; ii < R + 2; ++ii)
 #pragma unroll
-            for (int cc = 0; cc < C + 2; ++cc) A[ii][cc] = ab[(int64_t)ii * g.lda + cc];
+            for (int c = 0; c < C; ++c) A[ii][c] = ab[(int64_t)ii * g.lda + c];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 x[i][c] = xin[base + (int64_t)i * ld + c];
                 fv[i][c] = f[base + (int64_t)i * ld + c];
-                fe[i][c] = 0.5 * (A[i + 1][c + 1] + A[i + 1][c + 2]) * g.ihx2;
-                fn[i][c] = 0.5 * (A[i + 1][c + 1] + A[i + 2][c + 1]) * g.ihy2;
             }
-            fw0[i] = 0.5 * (A[i + 1][1] + A[i + 1][0]) * g.ihx2;
+            aw[i] = j == 0 ? ab[(int64_t)(i + 1) * g.lda - 1] : 0.0;
+            ae[i] = j == 15 ? ab[(int64_t)(i + 1) * g.lda + C] : 0.0;
             hw[i] = (j == 0 && c0 > 0) ? xin[base + (int64_t)i * ld - 1] : 0.0;
             he[i] = (j == 15 && c0 + TX < g.nx) ? xin[base + (int64_t)i * ld + C] : 0.0;
         }
 #pragma unroll
-        for (int c = 0; c < C; ++c) fs0[c] = 0.5 * (A[1][c + 1] + A[0][c + 1]) * g.ihy2;
+        for (int i = 0; i < R; ++i) {
+            aw[i] = dpp_keep<kDppRowShr1>(aw[i], A[i + 1][C - 1]);
+            ae[i] = dpp_keep<kDppRowShl1>(ae[i], A[i + 1][0]);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                fe[i][c] = 0.5 * (A[i + 1][c] + (c + 1 < C ? A[i + 1][c + 1] : ae[i])) * g.ihx2;
+                fn[i][c] = 0.5 * (A[i + 1][c] + A[i + 2][c]) * g.ihy2;
+            }
+            fw0[i] = 0.5 * (A[i + 1][0] + aw[i]) * g.ihx2;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) fs0[c] = 0.5 * (A[1][c] + A[0][c]) * g.ihy2;
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
@@ -238,10 +248,12 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
         for (int c = 0; c < C; ++c)
             s_halo[1][lcol(c)] = r0 + TY < g.ny ? xin[(int64_t)(r0 + TY) * ld + c0 + lc0 + c] : 0.0;
     }
-    const int rlo = axis_own_begin(g.ny, TY, g.oy, bi) - r0 - lr0;
-    const int rhi = axis_own_end(g.ny, TY, g.oy, bi, g.nty) - r0 - lr0;
-    const int clo = axis_own_begin(g.nx, TX, g.ox, bj) - c0 - lc0;
-    const int chi = axis_own_end(g.nx, TX, g.ox, bj, g.ntx) - c0 - lc0;
+    // owned rows and columns of the tile (uniform)
+    const int orlo = axis_own_begin(g.ny, TY, g.oy, bi) - r0;
+    const int orhi = axis_own_end(g.ny, TY, g.oy, bi, g.nty) - r0;
+    const int oclo = axis_own_begin(g.nx, TX, g.ox, bj) - c0;
+    const int ochi = axis_own_end(g.nx, TX, g.ox, bj, g.ntx) - c0;
+    const int rlo = orlo - lr0, rhi = orhi - lr0, clo = oclo - lc0, chi = ochi - lc0;
 
     double up[C], dn[C];
     // publish this group's first / last rows for the sweep of parity par and
@@ -290,7 +302,7 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
                     const double xc = x[i][c];
                     const double ax = (w * (xc - uw) + fe[i][c] * (xc - ue)) + (sf * (xc - us) + fn[i][c] * (xc - un));
                     const double rr = fv[i][c] - ax;
-                    rsq += rr * rr;
+                    rsq = __builtin_fma(rr, rr, rsq);
                 }
                 nw[c] = (fv[i][c] + ((w * uw + fe[i][c] * ue) + (sf * us + fn[i][c] * un))) * di[i][c];
             }
@@ -299,35 +311,63 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
                 prev[c] = x[i][c];
                 x[i][c] = nw[c];
             }
+            if (FIRST && RES) pin(rsq);
         }
     };
+    // Two sub-iterations per loop trip: the exchange's LDS buffer is then a
+    // constant and the two sweeps trade the rows' registers.
     exchange(0);
     sweep(std::true_type{});
-    for (int it = 1; it < nsub; ++it) {
-        exchange(it & 1);
+    int it = 1;
+    for (; it + 1 < nsub; it += 2) {
+        exchange(1);
+        sweep(std::false_type{});
+        exchange(0);
+        sweep(std::false_type{});
+    }
+    if (it < nsub) {
+        exchange(1);
         sweep(std::false_type{});
     }
 
-    // step 3: owned points back to global memory
+    // step 3: owned points back to global memory (the lane's place formed
+    // again from its index, so that it holds no registers through the sweeps)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int wr = (tid >> 4) * R, wc = (tid & 15) * C;
+    double *out = xout + (int64_t)(r0 + wr) * ld + c0 + wc;
 #pragma unroll
     for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            if (i >= rlo && i < rhi && c >= clo && c < chi) xout[base + (int64_t)i * ld + c] = x[i][c];
+        if (i >= orlo - wr && i < orhi - wr) store_run<double, C>(out + (int64_t)i * ld, x[i], oclo - wc, ochi - wc);
     return rsq;
 }
 
-// One cycle of tile `tile`: the register body when the grid holds a full
-// tile in each direction (and g.reg), else the LDS body.
-template <int TX, int TY, bool RES>
+// Whether a grid takes the register body: it holds a full tile in each
+// direction, and the caller did not ask for the LDS one.
+inline bool vc_reg(const GeomVC &g) { return g.reg && g.nx >= g.tx && g.ny >= g.ty; }
+
+// Minimum wavefronts per SIMD asked for: the register body fits 128 VGPRs at
+// 64-wide tiles and 80 at 32-wide ones (us per cycle of 8 right-hand sides at
+// 1024^2, s = 8, o = 14: 64 x 64 134 -> 96, 32 x 64 129 -> 118, 32 x 32 155 ->
+// 149, 64 x 32 unchanged).
+template <int TX, bool REG>
+constexpr int vc_min_waves()
+{
+    return !REG ? 1 : TX == 64 ? 4 : TX == 32 ? 6 : 1;
+}
+
+// One cycle of tile `tile` by the register body (REG, grids that vc_reg
+// admits) or the LDS body.  Kernels hold one of them each: with both, every
+// launch had the LDS body's registers (five weights a point: 156 at 64-wide
+// tiles, three wavefronts a SIMD).
+template <int TX, int TY, bool RES, bool REG>
 __device__ __forceinline__ double tile_vc(const GeomVC &g, int tile, const double *__restrict__ f,
                                           const double *__restrict__ xin, double *__restrict__ xout, int nsub)
 {
     using S = VcShape<TX, TY>;
-    char *pool = lds_pool<vc_lds_bytes<TX, TY>()>();
-    if (g.reg && g.nx >= TX && g.ny >= TY)
-        return reg_tile_vc<S::C, S::R, S::W, RES>(g, tile, f, xin, xout, nsub, pool);
-    return lds_tile_vc<TX, TY, RES>(g, tile, f, xin, xout, nsub, pool);
+    char *pool = lds_pool<vc_lds_bytes<TX, TY, REG>()>();
+    if constexpr (REG) return reg_tile_vc<S::C, S::R, S::W, RES>(g, tile, f, xin, xout, nsub, pool);
+    else return lds_tile_vc<TX, TY, RES>(g, tile, f, xin, xout, nsub, pool);
 }
 
 // Tile shapes of the variable-coefficient cycle.

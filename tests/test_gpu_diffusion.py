@@ -303,3 +303,27 @@ def test_vc_config_size_forward_and_adjoint_match_oracle(orc):
     err = np.max(np.abs(g - want_g)) / np.max(np.abs(want_g))
     say(f"1024^2 x 16: dL/da max difference {err:.2e} of the largest entry")
     assert err <= 1e-12
+
+
+@pytest.mark.parametrize("n,tile,ov", [((3000, 2503), (64, 32), (14, 14)), ((130, 97), (64, 64), (6, 4)),
+                                       ((64, 64), (64, 64), (0, 0)), ((33, 47), (32, 32), (5, 3)), ((40, 64), (64, 32), (2, 2))])
+@pytest.mark.parametrize("s", [1, 2, 5])
+def test_vc_cycle_bodies_match_oracle(orc, n, tile, ov, s):
+    """A grid walked in strips, whole and ragged register tiles, a grid below the tile
+    (LDS body); odd and even sub-iterations (two per loop trip)."""
+    nx, ny = n
+    if nx > 1000 and s != 2:
+        pytest.skip("one sub-iteration count at the large size")
+    hx, hy = 1.0 / (nx + 1), 1.2 / (nx + 1)
+    rng = np.random.default_rng(3)
+    a = np.exp(0.5 * rng.standard_normal((ny + 2, nx + 2)))
+    f, u0 = rng.standard_normal((ny, nx)), rng.standard_normal((ny, nx))
+    say(f"vc bodies {n} {tile} {ov} s={s}")
+    nc = 2
+    want = orc.vc_solve_2d(a, f, u0, hx, hy, tile=tile, s=s, tol=-1.0, max_cycles=nc, overlap=ov)[0]
+    for lds in (False, True):
+        for tol in (0.0, 1e-100):
+            U = dev(u0)
+            hj.solve_vc_2d(dev(a), dev(f), U, hx=hx, hy=hy, tile=tile, s=s, overlap=ov, rel_tol=tol, max_cycles=nc,
+                           allow_not_converged=True, lds_kernel=lds)
+            assert np.array_equal(host(U), want), (lds, tol)
