@@ -192,43 +192,31 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
     };
 
     // step 1: x, f, the x-halo and the face weights into registers, the
-    // frozen halo rows into LDS.  Row ii of A holds the nodes of points
-    // (r0 + lr0 + ii - 1, c0 + lc0 + c); the node columns beside the lane's
-    // come from the lanes beside it (aw, ae: the row group's ends load theirs),
-    // so a node row is read once per row group in 16-byte pieces.
+    // frozen halo rows into LDS.  ab[ii * lda + cc] is the node of interior
+    // point (r0 + lr0 + ii - 1, c0 + lc0 + cc - 1).
     double x[R][C], fv[R][C], fe[R][C], fn[R][C], di[R][C], fw0[R], fs0[C], hw[R], he[R];
     {
-        const double *ab = g.a + (int64_t)(r0 + lr0) * g.lda + (c0 + lc0 + 1);
-        double A[R + 2][C], aw[R], ae[R];
+        const double *ab = g.a + (int64_t)(r0 + lr0) * g.lda + (c0 + lc0);
+        double A[R + 2][C + 2];
 #pragma unroll
         for (int ii = 0; ii < R + 2; ++ii)
 #pragma unroll
-            for (int c = 0; c < C; ++c) A[ii][c] = ab[(int64_t)ii * g.lda + c];
+            for (int cc = 0; cc < C + 2; ++cc) A[ii][cc] = ab[(int64_t)ii * g.lda + cc];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 x[i][c] = xin[base + (int64_t)i * ld + c];
                 fv[i][c] = f[base + (int64_t)i * ld + c];
+                fe[i][c] = 0.5 * (A[i + 1][c + 1] + A[i + 1][c + 2]) * g.ihx2;
+                fn[i][c] = 0.5 * (A[i + 1][c + 1] + A[i + 2][c + 1]) * g.ihy2;
             }
-            aw[i] = j == 0 ? ab[(int64_t)(i + 1) * g.lda - 1] : 0.0;
-            ae[i] = j == 15 ? ab[(int64_t)(i + 1) * g.lda + C] : 0.0;
+            fw0[i] = 0.5 * (A[i + 1][1] + A[i + 1][0]) * g.ihx2;
             hw[i] = (j == 0 && c0 > 0) ? xin[base + (int64_t)i * ld - 1] : 0.0;
             he[i] = (j == 15 && c0 + TX < g.nx) ? xin[base + (int64_t)i * ld + C] : 0.0;
         }
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            aw[i] = dpp_keep<kDppRowShr1>(aw[i], A[i + 1][C - 1]);
-            ae[i] = dpp_keep<kDppRowShl1>(ae[i], A[i + 1][0]);
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                fe[i][c] = 0.5 * (A[i + 1][c] + (c + 1 < C ? A[i + 1][c + 1] : ae[i])) * g.ihx2;
-                fn[i][c] = 0.5 * (A[i + 1][c] + A[i + 2][c]) * g.ihy2;
-            }
-            fw0[i] = 0.5 * (A[i + 1][0] + aw[i]) * g.ihx2;
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c) fs0[c] = 0.5 * (A[1][c] + A[0][c]) * g.ihy2;
+        for (int c = 0; c < C; ++c) fs0[c] = 0.5 * (A[1][c + 1] + A[0][c + 1]) * g.ihy2;
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
@@ -314,20 +302,30 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
             if (FIRST && RES) pin(rsq);
         }
     };
-    // Two sub-iterations per loop trip: the exchange's LDS buffer is then a
-    // constant and the two sweeps trade the rows' registers.
     exchange(0);
     sweep(std::true_type{});
     int it = 1;
-    for (; it + 1 < nsub; it += 2) {
-        exchange(1);
-        sweep(std::false_type{});
-        exchange(0);
-        sweep(std::false_type{});
-    }
-    if (it < nsub) {
-        exchange(1);
-        sweep(std::false_type{});
+    if constexpr (C < 4) {
+        // Two sub-iterations per loop trip: the exchange's LDS buffer is then
+        // a constant and the two sweeps trade the rows' registers (32 x 64,
+        // 8 right-hand sides at 1024^2: 119 us a cycle against 124).  At four
+        // columns a lane the longer body spills: 64 x 32 takes 239 us a cycle
+        // of 16 right-hand sides in place of 229.
+        for (; it + 1 < nsub; it += 2) {
+            exchange(1);
+            sweep(std::false_type{});
+            exchange(0);
+            sweep(std::false_type{});
+        }
+        if (it < nsub) {
+            exchange(1);
+            sweep(std::false_type{});
+        }
+    } else {
+        for (; it < nsub; ++it) {
+            exchange(it & 1);
+            sweep(std::false_type{});
+        }
     }
 
     // step 3: owned points back to global memory (the lane's place formed
@@ -347,9 +345,9 @@ __device__ __forceinline__ double reg_tile_vc(const GeomVC &g, int tile, const d
 inline bool vc_reg(const GeomVC &g) { return g.reg && g.nx >= g.tx && g.ny >= g.ty; }
 
 // Minimum wavefronts per SIMD asked for: the register body fits 128 VGPRs at
-// 64-wide tiles and 80 at 32-wide ones (us per cycle of 8 right-hand sides at
-// 1024^2, s = 8, o = 14: 64 x 64 134 -> 96, 32 x 64 129 -> 118, 32 x 32 155 ->
-// 149, 64 x 32 unchanged).
+// 64-wide tiles and 80 at 32-wide ones (us per cycle at 1024^2, s = 8, o = 14;
+// 8 right-hand sides: 64 x 64 134 -> 88, 32 x 64 126 -> 119, 32 x 32 155 ->
+// 149; 16 right-hand sides: 64 x 32 236 -> 229).
 template <int TX, bool REG>
 constexpr int vc_min_waves()
 {
