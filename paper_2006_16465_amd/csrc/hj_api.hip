@@ -456,7 +456,7 @@ struct BatchScratch {
     int64_t nstate = 0;
     hj::BState *host = nullptr;  // 2 x nhost pinned
     int64_t nhost = 0;
-    void *wg = nullptr;  // one-workgroup 1D batches: problem table and states
+    void *wg = nullptr;  // one-workgroup batches: problem table (1D) and states
     size_t wg_bytes = 0;
 };
 
@@ -471,6 +471,17 @@ hj_status grow_dev(T *&ptr, int64_t &have, int64_t need)
     have = 0;
     HJ_HIP(hipMalloc((void **)&ptr, (size_t)need * sizeof(T)));
     have = need;
+    return HJ_OK;
+}
+
+hj_status wg_ensure(BatchScratch &B, size_t need)
+{
+    if (need <= B.wg_bytes) return HJ_OK;
+    if (B.wg) HJ_HIP(hipFree(B.wg));
+    B.wg = nullptr;
+    B.wg_bytes = 0;
+    HJ_HIP(hipMalloc(&B.wg, need));
+    B.wg_bytes = need;
     return HJ_OK;
 }
 
@@ -863,6 +874,62 @@ hj_status run_batch(const hj_problem *probs, int64_t nprob, hj_dtype dt, double 
     return HJ_OK;
 }
 
+// Cycles per launch of a one-workgroup solve (bounds the time of a launch).
+constexpr int64_t kWgChunk = 4096;
+
+// Solve every right-hand side in a workgroup of its own (see
+// hj_solve_vc_wg.hip): the iterates, cycle counts and infos of the paths
+// below.  A batch judges every iterate also without a tolerance, as
+// solve_vc_batched does (a right-hand side that is not finite stops there).
+hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const hj_params &P, hipStream_t st,
+                      BatchScratch &B, hj_info *infos)
+{
+    const hj::GeomVC g = make_geom_vc(pr, P);
+    const size_t need = (size_t)pr.batch * sizeof(hj::Ctrl);
+    hj_status r;
+    if ((r = wg_ensure(B, need)) != HJ_OK) return r;
+    hj::Ctrl *ctrls = (hj::Ctrl *)B.wg;
+    HJ_HIP(hj::launch_ctrl_init_n(ctrls, pr.batch, st));
+    const int64_t maxc = P.max_cycles;
+    const bool judged = P.rel_tol > 0.0, every = judged || pr.batch > 1;
+    std::vector<hj::Ctrl> hc((size_t)pr.batch);
+    auto read_back = [&]() -> hj_status {
+        HJ_HIP(hipMemcpyAsync(hc.data(), ctrls, need, hipMemcpyDeviceToHost, st));
+        HJ_HIP(hipStreamSynchronize(st));
+        return HJ_OK;
+    };
+    for (int64_t cb = 0;;) {
+        const int64_t ce = maxc - cb < kWgChunk ? maxc + 1 : cb + kWgChunk;
+        HJ_HIP(hj::launch_solve_vc_wg(g, pr.batch, pr.batch > 1 ? pr.batch_stride : 0, P.s, f, u, cb, ce, maxc,
+                                      judged ? P.rel_tol : -1.0, every, ctrls, st));
+        if (ce == maxc + 1) break;
+        if (every) {
+            if ((r = read_back()) != HJ_OK) return r;
+            if (std::none_of(hc.begin(), hc.end(), [](const hj::Ctrl &c) { return c.status == hj::ST_RUNNING; }))
+                break;
+        }
+        cb = ce;
+    }
+    if ((r = read_back()) != HJ_OK) return r;
+    hj_status worst = HJ_OK;
+    for (int b = 0; b < pr.batch; ++b) {
+        const hj::Ctrl &c = hc[(size_t)b];
+        const int64_t used = every && c.status != hj::ST_RUNNING ? c.done_cycle : maxc;
+        if (infos) {
+            infos[b].cycles = used;
+            infos[b].sweeps = used * P.s;
+            infos[b].r0_norm = std::sqrt(c.r0sq);
+            infos[b].rel_residual = c.r0sq > 0.0 ? std::sqrt(c.last_rsq) / std::sqrt(c.r0sq) : 0.0;
+            if (!std::isfinite(c.last_rsq)) infos[b].rel_residual = NAN;
+        }
+        if (c.status == hj::ST_NONFINITE) worst = HJ_ERR_NONFINITE;
+        else if (c.status != hj::ST_CONVERGED && judged && worst == HJ_OK) worst = HJ_ERR_NOT_CONVERGED;
+    }
+    if (worst == HJ_ERR_NONFINITE) return fail(worst, "residual norm became non-finite");
+    if (worst == HJ_ERR_NOT_CONVERGED) return fail(worst, "max_cycles reached before rel_tol");
+    return HJ_OK;
+}
+
 // Several right-hand sides of one variable-coefficient operator: each is a
 // problem of the batched engine (one launch per cycle for all of them, each
 // judged on its own), so every right-hand side gets the iterates and the
@@ -1243,8 +1310,6 @@ hj_status hj_solve_2d_refined(int64_t nx, int64_t ny, int64_t ld, double hx, dou
 // The whole 1D solve in one workgroup: cycles run in chunks of kWgChunk per
 // launch (a few ms of GPU time), the solve state carried in S.ctrl.  Same stop
 // rule, iterates and info as drive().
-static constexpr int64_t kWgChunk = 4096;
-
 static hj_status drive_1d_wg(const hj::Geom1 &g, int dt, const hj_params &p, const void *f, void *x, hipStream_t st,
                       DevScratch &S, hj_info *info)
 {
@@ -1635,13 +1700,8 @@ static hj_status solve_batched_wg1d(const hj_problem *probs, int64_t nprob, cons
     }
     const size_t tbytes = ((size_t)nprob * sizeof(hj::WgProb) + 255) / 256 * 256;
     const size_t need = tbytes + (size_t)nprob * sizeof(hj::Ctrl);
-    if (need > B.wg_bytes) {
-        if (B.wg) HJ_HIP(hipFree(B.wg));
-        B.wg = nullptr;
-        B.wg_bytes = 0;
-        HJ_HIP(hipMalloc(&B.wg, need));
-        B.wg_bytes = need;
-    }
+    hj_status r;
+    if ((r = wg_ensure(B, need)) != HJ_OK) return r;
     hj::WgProb *dprobs = (hj::WgProb *)B.wg;
     hj::Ctrl *ctrls = (hj::Ctrl *)((char *)B.wg + tbytes);
     HJ_HIP(hipMemcpyAsync(dprobs, table.data(), (size_t)nprob * sizeof(hj::WgProb), hipMemcpyHostToDevice, st));
@@ -1656,7 +1716,6 @@ static hj_status solve_batched_wg1d(const hj_problem *probs, int64_t nprob, cons
         HJ_HIP(hipStreamSynchronize(st));
         return HJ_OK;
     };
-    hj_status r;
     for (int64_t cb = 0;;) {
         const int64_t ce = maxc - cb < kWgChunk ? maxc + 1 : cb + kWgChunk;
         HJ_HIP(hj::launch_solve1d_wg_batch(dt, P1.tile_x, dprobs, nprob, max_n, max_nt, P1.s, cb, ce, maxc, tol,
@@ -1823,6 +1882,9 @@ hj_status hj_solve_vc_2d(const hj_vc_problem *prob, const double *f, double *u, 
     if ((r = check_device_ptr(u, dev, "u")) != HJ_OK) return r;
     DevScratch &S = g_scr[dev];
     std::lock_guard<std::mutex> lock(S.mu);
+    if (p->method == HJ_HIERARCHICAL && !(p->flags & HJ_FLAG_LAUNCH_PER_CYCLE) &&
+        hj::solve_vc_wg_supported(make_geom_vc(*prob, *p), p->s))
+        return solve_vc_wg(*prob, f, u, *p, (hipStream_t)stream, g_bat[dev], infos);
     if (p->method == HJ_HIERARCHICAL && prob->batch > 1)
         return solve_vc_batched(*prob, f, u, *p, (hipStream_t)stream, dev, S, infos);
     return solve_vc_locked(*prob, f, u, *p, (hipStream_t)stream, S, infos);

@@ -103,6 +103,14 @@ struct GeomVC {
     double ihx2, ihy2;
     int reg;          // 1: register-resident tiles where the grid holds a full tile
 };
+// Whole hierarchical solves of `batch` right-hand sides (`stride` elements
+// apart), one workgroup and one control block each: cycles [c_begin, c_end)
+// as in launch_solve1d_wg.  Supported: grids up to 64 x 64 whose cycle is s
+// sweeps of the whole grid, without HJ_FLAG_LDS_KERNEL (g.reg).
+bool solve_vc_wg_supported(const GeomVC &g, int s);
+hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
+                              int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls,
+                              hipStream_t st);
 int64_t cycle_vc_blocks(const GeomVC &g);
 int64_t sweep_vc_blocks(const GeomVC &g);
 hipError_t launch_cycle_vc(const GeomVC &g, int s, bool res, const double *f, const double *xin,

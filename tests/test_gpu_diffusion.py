@@ -327,3 +327,61 @@ def test_vc_cycle_bodies_match_oracle(orc, n, tile, ov, s):
             hj.solve_vc_2d(dev(a), dev(f), U, hx=hx, hy=hy, tile=tile, s=s, overlap=ov, rel_tol=tol, max_cycles=nc,
                            allow_not_converged=True, lds_kernel=lds)
             assert np.array_equal(host(U), want), (lds, tol)
+
+
+# heights on both sides of every row count a wavefront (16, 24, 32, 48, 64),
+# widths below and at 64, and one step past the one-workgroup solve (65)
+@pytest.mark.parametrize("nx,ny", [(64, 64), (63, 64), (64, 63), (1, 1), (3, 2), (64, 16), (40, 17), (64, 24), (33, 25),
+                                   (64, 32), (17, 33), (64, 48), (5, 49), (65, 20), (20, 65)])
+@pytest.mark.parametrize("s", [1, 2, 3, 8])
+def test_vc_one_workgroup_solves_match_oracle(orc, nx, ny, s):
+    rng = np.random.default_rng(nx + 100 * ny + s)
+    hx, hy = 1.0 / (nx + 1), 0.9 / (ny + 1)
+    a = np.exp(0.5 * rng.standard_normal((ny + 2, nx + 2)))
+    f, u0 = rng.standard_normal((3, ny, nx)), rng.standard_normal((3, ny, nx))
+    kw = dict(tile=(32, 32), s=s, overlap=(2 * s - 2, 2 * s - 1))
+    say(f"vc one workgroup {nx} x {ny} s={s}")
+    for nb in (1, 3):
+        for tol, cap in ((0.0, 5), (1e-100, 4), (0.3, 10_000)):
+            U = dev(u0[:nb])
+            infos = hj.solve_vc_2d(dev(a), dev(f[:nb]), U, hx=hx, hy=hy, rel_tol=tol, max_cycles=cap,
+                                   allow_not_converged=True, **kw)
+            got = host(U)
+            for b in range(nb):
+                xo, co, relo, r0o = orc.vc_solve_2d(a, f[b], u0[b], hx, hy, tol=tol, max_cycles=cap, **kw)
+                assert np.array_equal(got[b], xo), (nb, b, tol)
+                assert infos[b].cycles == (co if co >= 0 else cap)
+                # the norms' sums run in another order than the oracle's, over
+                # at most 65 x 64 squares: 4160 x 2^-53 of each, on either side
+                assert abs(infos[b].r0_norm - r0o) <= 1e-12 * r0o
+                assert abs(infos[b].rel_residual - relo) <= 2e-12 * relo
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (61, 45)])
+def test_vc_one_workgroup_not_finite_and_long_runs(nx, ny):
+    """Where a solve stops and what it holds when values overflow or are NaN, and
+    over more cycles than one launch runs, as by the tile kernels."""
+    rng = np.random.default_rng(5)
+    h = 1.0 / (nx + 1)
+    a = np.exp(rng.standard_normal((ny + 2, nx + 2)))
+    f, u0 = rng.standard_normal((2, ny, nx)), rng.standard_normal((2, ny, nx))
+    bad = u0.copy()
+    bad[0, 7, nx - 1], bad[1, ny - 1, 3] = np.inf, np.nan
+    big = u0 * 1e150
+    big[:, ny - 1, nx - 1] = -1e160
+    for name, x0, tol, cap, s in (("inf", bad, 0.0, 3, 4), ("inf", bad, 1e-9, 9, 4), ("overflow", big, 0.0, 3, 4),
+                                  ("long", u0, 0.0, 4200, 1), ("long", u0, 1e-100, 4200, 1)):
+        for nb in (1, 2):
+            say(f"vc one workgroup {name} {nx} x {ny} tol={tol} x{nb}")
+            out = []
+            for lds in (False, True):
+                U = dev(x0[:nb])
+                try:
+                    infos = hj.solve_vc_2d(dev(a), dev(f[:nb]), U, hx=h, hy=h, tile=(64, 32), s=s, overlap=(0, 14),
+                                           rel_tol=tol, max_cycles=cap, allow_not_converged=True, lds_kernel=lds)
+                    st = [(i.status, i.cycles) for i in infos]
+                except hj.HJError as e:
+                    st = str(e)
+                out.append((st, host(U)))
+            assert out[0][0] == out[1][0], name
+            assert np.array_equal(out[0][1], out[1][1], equal_nan=True), name

@@ -189,3 +189,32 @@ def test_grf_statistics():
     lag = 13
     c = np.mean(g[:, :-lag] * g[:, lag:]) / np.var(g)
     assert abs(c - np.exp(-(lag / 257) ** 2 / (2 * 0.05 ** 2))) <= 0.15
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("s", [1, 2, 3, 5, 8])
+def test_cycle_is_whole_grid_sweeps_where_the_overlap_reaches(orc, axis, s):
+    """The rule by which small solves run whole in one workgroup: with one tile, or
+    overlap >= 2 s - 2, a cycle is s classical sweeps of the whole grid bit for
+    bit, and with a smaller overlap on more than one tile it is not."""
+    rng = np.random.default_rng(s)
+    for tile in (16, 32):
+        for n in (1, 2, tile - 1, tile, tile + 1, tile + 3, 2 * tile - 1, 47, 64):
+            m = 5
+            nx, ny = (n, m) if axis == 0 else (m, n)
+            h = 1.0 / (n + 1)
+            a = np.exp(rng.standard_normal((ny + 2, nx + 2)))
+            f, x0 = rng.standard_normal((ny, nx)), rng.standard_normal((ny, nx))
+            x0[ny // 2, nx // 2] = np.inf  # values that are not finite spread alike
+            want = x0
+            for _ in range(2):
+                want = orc.vc_solve_2d(a, f, want, h, h, method=orc.CLASSICAL, tol=0.0, max_cycles=s)[0]
+            for o in sorted({0, 2 * s - 3, 2 * s - 2, 2 * s - 1, tile - 1}):
+                if not 0 <= o < tile:
+                    continue
+                t, ov = ((tile, 16), (o, 0)) if axis == 0 else ((16, tile), (0, o))
+                got = orc.vc_solve_2d(a, f, x0, h, h, tile=t, s=s, overlap=ov, tol=0.0, max_cycles=2)[0]
+                if n <= tile or o >= 2 * s - 2:
+                    assert np.array_equal(got, want, equal_nan=True), (tile, n, o)
+                elif o == 0 and n == 64:
+                    assert not np.array_equal(got, want, equal_nan=True), (tile, n, o)
