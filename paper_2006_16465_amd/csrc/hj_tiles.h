@@ -510,12 +510,16 @@ __device__ __forceinline__ float dpp_move(float old, float v)
 // One sweep from a to b: b_i = (h^2 f_i + (a_{i-1} + a_{i+1})) / 2 in the FMA
 // form fma(a_{i-1} + a_{i+1}, 1/2, h^2 f_i / 2) (equal bit for bit while the
 // values are normal numbers: halving is exact and commutes with rounding).
+// lft and rgt are the neighbours of the lane's run; lanes 0 and 63, which the
+// shifts have no source for, keep the frozen halo in them from sweep to sweep
+// (a shift into a fresh copy of the halo adds two moves to every four FP64
+// instructions of a point pair).
 template <typename T, int P, bool MASK>
-__device__ __forceinline__ void reg_sweep_1d(const T (&a)[P], T (&b)[P], const T (&fh)[P], T haloL, T haloR,
+__device__ __forceinline__ void reg_sweep_1d(const T (&a)[P], T (&b)[P], const T (&fh)[P], T &lft, T &rgt,
                                              int l0, int ni)
 {
-    const T lft = dpp_move<kDppWaveShr1>(haloL, a[P - 1]);
-    const T rgt = dpp_move<kDppWaveShl1>(haloR, a[0]);
+    lft = dpp_move<kDppWaveShr1>(lft, a[P - 1]);
+    rgt = dpp_move<kDppWaveShl1>(rgt, a[0]);
 #pragma unroll
     for (int i = 0; i < P; ++i) {
         const T w = i > 0 ? a[i - 1] : lft;
@@ -532,7 +536,7 @@ __device__ __forceinline__ void reg_sweep_1d(const T (&a)[P], T (&b)[P], const T
 // points); points at or past ni read and stay 0.
 template <typename T, int P, bool RES, bool MASK>
 __device__ __forceinline__ double reg_tile_1d(const Geom1 &g, const T *__restrict__ fp, const T *__restrict__ xp,
-                                              T *__restrict__ op, T haloL, T haloR, int l0, int ni, int lo,
+                                              T *__restrict__ op, T lft, T rgt, int l0, int ni, int lo,
                                               int hi, int s)
 {
     const T hh = T(g.hh);
@@ -547,8 +551,8 @@ __device__ __forceinline__ double reg_tile_1d(const Geom1 &g, const T *__restric
             fv[i] = in ? fp[i] : T(0);
         }
         if (RES) {
-            const T lft = dpp_move<kDppWaveShr1>(haloL, xa[P - 1]);
-            const T rgt = dpp_move<kDppWaveShl1>(haloR, xa[0]);
+            lft = dpp_move<kDppWaveShr1>(lft, xa[P - 1]);
+            rgt = dpp_move<kDppWaveShl1>(rgt, xa[0]);
 #pragma unroll
             for (int i = 0; i < P; ++i) {
                 const int lc = l0 + i;
@@ -565,11 +569,11 @@ __device__ __forceinline__ double reg_tile_1d(const Geom1 &g, const T *__restric
     }
     int k = 0;
     for (; k + 1 < s; k += 2) {
-        reg_sweep_1d<T, P, MASK>(xa, xb, fh, haloL, haloR, l0, ni);
-        reg_sweep_1d<T, P, MASK>(xb, xa, fh, haloL, haloR, l0, ni);
+        reg_sweep_1d<T, P, MASK>(xa, xb, fh, lft, rgt, l0, ni);
+        reg_sweep_1d<T, P, MASK>(xb, xa, fh, lft, rgt, l0, ni);
     }
     if (k < s) {
-        reg_sweep_1d<T, P, MASK>(xa, xb, fh, haloL, haloR, l0, ni);
+        reg_sweep_1d<T, P, MASK>(xa, xb, fh, lft, rgt, l0, ni);
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             const int lc = l0 + i;
