@@ -55,7 +55,7 @@ struct DevScratch {
     void *rbuf = nullptr;  // mixed precision: FP32 residual and correction
     size_t rbytes = 0;
     hj::Ctrl *ctrl = nullptr;
-    hj::Ctrl *host = nullptr;  // 2 pinned slots
+    hj::Ctrl *host = nullptr;  // pinned
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t tev[2] = {nullptr, nullptr};  // timing events of the autotuner
 };
@@ -67,7 +67,7 @@ hj_status scratch_ensure(DevScratch &S, size_t xbytes, int64_t npart, size_t rby
 {
     if (!S.ready) {
         HJ_HIP(hipMalloc((void **)&S.ctrl, sizeof(hj::Ctrl)));
-        HJ_HIP(hipHostMalloc((void **)&S.host, 2 * sizeof(hj::Ctrl), hipHostMallocDefault));
+        HJ_HIP(hipHostMalloc((void **)&S.host, sizeof(hj::Ctrl), hipHostMallocDefault));
         HJ_HIP(hipEventCreateWithFlags(&S.ev[0], hipEventDisableTiming));
         HJ_HIP(hipEventCreateWithFlags(&S.ev[1], hipEventDisableTiming));
         S.ready = true;
@@ -174,14 +174,14 @@ struct Step {
 };
 
 // Where a solve keeps its device control block and reduction partials, and how
-// the host reads the block: through two pinned slots and events (one batch of
+// the host learns of the verdict: through a pinned slot and events (one batch of
 // lookahead), or, without them (host == nullptr), by a copy into host memory
 // after each batch followed by a stream synchronisation.
 struct Ctl {
     hj::Ctrl *ctrl;
     double *partials;  // npart doubles: two halves, by cycle parity
     int64_t npart;
-    hj::Ctrl *host;    // 2 pinned slots, or nullptr
+    hj::Ctrl *host;    // pinned, or nullptr
     hipEvent_t ev[2];
 };
 
@@ -217,7 +217,10 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
     double *part[2] = {S.partials, S.partials + S.npart / 2};
     const int64_t maxc = p.max_cycles;
     hj_status r;
-    HJ_HIP(hj::launch_ctrl_init(S.ctrl, stream, p.rel_tol > 0.0 ? sw_tol : -1.0, sw_min_c));
+    // in tolerance mode the judge leaves its verdict in pinned memory
+    hj::Ctrl *const told = p.rel_tol > 0.0 ? S.host : nullptr;
+    if (told) told->status = hj::ST_RUNNING;
+    HJ_HIP(hj::launch_ctrl_init(S.ctrl, stream, p.rel_tol > 0.0 ? sw_tol : -1.0, sw_min_c, told));
     int64_t final_c = maxc;
     hj::Ctrl c{};
     if (p.rel_tol <= 0.0) {
@@ -229,13 +232,20 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
             HJ_HIP(st.cycle(bufs[k % 3], bufs[(k + 1) % 3], false, -1.0, none));
         HJ_HIP(st.resid(bufs[maxc % 3], part[1]));
         HJ_HIP(hj::launch_judge(part[1], st.nb_resid, S.ctrl, maxc, -1.0, stream));
+        if (maxc % 3 != 0) HJ_HIP(st.copy(xu, bufs[maxc % 3]));
         if ((r = read_ctrl(S, stream, c)) != HJ_OK) return r;
     } else {
         const double tol = p.rel_tol;
         int64_t next = 0;
-        // check_every > 0: fixed batch.  0: batches sized to about kBatchUs of
-        // GPU time from the cycle rate observed between polls, so that at most
-        // a batch or two of early-exit launches follow convergence.
+        // check_every > 0: fixed batch.  0: a batch or two of early-exit
+        // launches follow convergence (about 2 us each on a small grid), and
+        // every poll holds the stream up for some us; 1.3 sqrt(cycles so far)
+        // is near the batch that costs least of both, within what the host
+        // needs to stay ahead (60 us of GPU time at the cycle rate seen) and
+        // 0.5 ms.  150 x 101, 32 x 32 tiles, against batches of 0.5 ms from
+        // the first poll on and a copy of the control block a poll: 4 cycles
+        // 201 -> 94 us, 15 254 -> 174, 34 321 -> 283, 176 1145 -> 1052;
+        // 512 x 512, 363 cycles: 2801 -> 2770.
         constexpr double kBatchUs = 500.0;
         int64_t batch = p.check_every > 0 ? p.check_every : 4;
         auto launch_batch = [&]() -> hj_status {
@@ -257,19 +267,21 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
             const double us = std::chrono::duration<double, std::micro>(t_now - t_prev).count();
             if (done > 0 && us > 0.0) {
                 const double per = us / (double)done;
-                batch = std::max<int64_t>(4, std::min<int64_t>(256, (int64_t)(kBatchUs / per)));
+                const int64_t most = std::min<int64_t>(256, (int64_t)(kBatchUs / per));
+                const int64_t least = std::max<int64_t>(4, (int64_t)(60.0 / per));
+                batch = std::max(least, std::min(most, (int64_t)(1.3 * std::sqrt((double)iter_now))));
             }
             t_prev = t_now;
             iter_prev = iter_now;
         };
-        if (S.host) {
+        if (told) {
             // one batch of lookahead: the next batch is enqueued before the
-            // host waits for the control block copied after the current one
+            // host waits for the event after the current one
+            int64_t upto[2] = {0, 0};
             auto enqueue = [&](int slot) -> hj_status {
                 hj_status e;
                 if ((e = launch_batch()) != HJ_OK) return e;
-                S.host[slot].iter = -1;
-                HJ_HIP(hipMemcpyAsync(&S.host[slot], S.ctrl, sizeof(hj::Ctrl), hipMemcpyDeviceToHost, stream));
+                upto[slot] = next;
                 HJ_HIP(hipEventRecord(S.ev[slot], stream));
                 return HJ_OK;
             };
@@ -279,12 +291,18 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
                 const bool more = next < maxc;
                 if (more && (r = enqueue(slot ^ 1)) != HJ_OK) return r;  // keep the GPU fed
                 HJ_HIP(hipEventSynchronize(S.ev[slot]));
-                if (S.host[slot].status != hj::ST_RUNNING || !more) break;
-                adapt(S.host[slot].iter);
+                // a verdict is final (later launches change nothing) and its
+                // other fields were written before its status
+                if (__atomic_load_n(&told->status, __ATOMIC_ACQUIRE) != hj::ST_RUNNING) {
+                    c = *told;
+                    break;
+                }
+                if (!more) break;
+                adapt(upto[slot]);
                 slot ^= 1;
             }
         } else {
-            // no pinned slots or events: the stream drains after every batch
+            // no pinned memory or events: the stream drains after every batch
             for (;;) {
                 if ((r = launch_batch()) != HJ_OK) return r;
                 if ((r = read_ctrl(S, stream, c)) != HJ_OK) return r;
@@ -292,7 +310,6 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
                 adapt(c.iter);
             }
         }
-        if ((r = read_ctrl(S, stream, c)) != HJ_OK) return r;
         if (c.status == hj::ST_RUNNING) {
             // every cycle ran: judge the last two iterates here
             HJ_HIP(hj::launch_judge(part[(maxc - 1) & 1], st.nb_cycle, S.ctrl, maxc - 1, tol, stream));
@@ -303,12 +320,12 @@ hj_status drive(const Step &st, void *xu, void *xs, size_t xbytes, const hj_para
         final_c = c.status != hj::ST_RUNNING ? c.done_cycle : maxc;
         if ((latest && c.status == hj::ST_CONVERGED) || c.status == hj::ST_SWITCH)
             final_c = std::min<int64_t>(c.done_cycle + 1, maxc);
-    }
-    if (status_out) *status_out = c.status;
-    if (final_c % 3 != 0) {
-        HJ_HIP(st.copy(xu, bufs[final_c % 3]));
+        if (final_c % 3 != 0) HJ_HIP(st.copy(xu, bufs[final_c % 3]));
+        // also for the launches that follow the stop: they read the control
+        // block, which the next solve starts anew
         HJ_HIP(hipStreamSynchronize(stream));
     }
+    if (status_out) *status_out = c.status;
     if (info) {
         info->cycles = final_c;
         info->sweeps = final_c * spc;

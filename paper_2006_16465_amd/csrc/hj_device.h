@@ -25,6 +25,10 @@ struct Ctrl {
     // tolerance.  The decision is taken once: sw_tol is set to -1 after it.
     double sw_tol;
     int64_t sw_min_c;
+    // Pinned host memory that gets the verdict when it falls (r0sq, last_rsq,
+    // done_cycle, then status), or nullptr.  A host that waits for an event
+    // between cycles finds it there without a copy on the stream.
+    Ctrl *host;
 };
 
 enum : int32_t { ST_RUNNING = 0, ST_CONVERGED = 1, ST_NONFINITE = 2, ST_LIMIT = 3, ST_SWITCH = 4 };
@@ -220,6 +224,12 @@ __device__ inline void judge(Ctrl *ctrl, int64_t c, double rsq, double tol)
         // start after the verdict return at once, as do all later kernels
         __hip_atomic_store(&ctrl->stop_at, c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ctrl->status, st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (Ctrl *const h = ctrl->host) {
+            h->r0sq = r0sq;
+            h->last_rsq = rsq;
+            h->done_cycle = c;
+            __hip_atomic_store(&h->status, st, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 

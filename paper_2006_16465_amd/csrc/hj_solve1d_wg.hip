@@ -302,6 +302,7 @@ __global__ void k_ctrl_init_n(Ctrl *ctrls, int64_t n)
     c.pad = 0;
     c.sw_tol = -1.0;
     c.sw_min_c = 0;
+    c.host = nullptr;
     ctrls[i] = c;
 }
 

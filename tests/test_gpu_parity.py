@@ -645,3 +645,30 @@ def test_strip_walk_reaches_every_tile(orc, n, tile, ov):
     say(f"strip walk {n} {tile} {ov}")
     got, _ = gpu_cycles_2d(f, x0, h, tile, 2, 2, ov)
     assert np.array_equal(got, orc.hier_2d(f, x0, h, h, tile, 2, 2, ov))
+
+
+@pytest.mark.parametrize("method", ["hierarchical", "global"])
+def test_stop_is_the_same_however_often_the_host_looks(orc, method):
+    """Solves that stop at iterate 0, 1, 2, ... and at the last one, with the host's
+    own batches, a look after every cycle, batches past the stop, and without
+    pinned memory (the allocation-free entry)."""
+    nx, ny = 90, 70
+    hx, hy = 1.0 / (nx + 1), 1.2 / (nx + 1)
+    rng = np.random.default_rng(11)
+    f, x0 = rng.standard_normal((ny, nx)), 1e-3 * rng.standard_normal((ny, nx))
+    kw = dict(hx=hx, hy=hy, tile=(32, 32), s=4, overlap=(6, 6), method=method, allow_not_converged=True)
+    rel = []
+    for k in range(24):
+        X = dev(x0)
+        rel.append(hj.solve_2d(dev(f), X, rel_tol=0.0, max_cycles=k, **kw).rel_residual if k else 1.0)
+    for want in [k for k in range(24) if all(rel[k] < r * (1 - 1e-9) for r in rel[:k])]:
+        tol = rel[want] * (1 + 1e-10)
+        X = dev(x0)
+        ref = hj.solve_2d(dev(f), X, rel_tol=0.0, max_cycles=max(want, 1), **kw)
+        ref = host(X) if want else x0
+        for solve, every, cap in ((hj.solve_2d, 0, 1000), (hj.solve_2d, 1, 1000), (hj.solve_2d, 500, 1000),
+                                  (hj.solve_2d, 0, max(want, 1)), (hj.solve_2d_noalloc, 0, 1000)):
+            X = dev(x0)
+            info = solve(dev(f), X, rel_tol=tol, max_cycles=cap, check_every=every, **kw)
+            assert info.cycles == want and info.status == hj.HJ_OK, (want, every, cap)
+            assert np.array_equal(host(X), ref), (want, every, cap)
