@@ -294,7 +294,7 @@ hipError_t cyc2(const Geom2 &g, int s, bool res, const void *f, const void *xin,
     if constexpr (RegShape<TX, TY>::ok) {
         if (g.reg && g.nx >= TX && g.ny >= TY) {
             using S = RegShape<TX, TY>;
-            using F = FewShape<TX, TY>;
+            using F = FewShape<T, TX, TY>;
             if constexpr (F::ok) {
                 if ((int64_t)g.ntx * g.nty * S::W <= kSimds)
                     return cyc2_reg<T, F::C, F::R, F::W, true>(g, s, res, f, xin, xout, red, tol, st);

@@ -651,11 +651,14 @@ struct RegShape {
 };
 
 // Shape for grids of few tiles: two rows a lane, so that a tile's sweep runs on
-// twice as many wavefronts.
-template <int TX, int TY>
+// twice as many wavefronts.  Not 128-wide tiles (interface rows of FP64 beyond
+// the LDS), and not 128-high ones in FP64, where eight wavefronts already
+// put two on every SIMD of the compute unit (us a cycle, four rows / two: 64 x 128 s = 16 overlap 22 at 512^2 14.1 / 15.1, s = 8
+// overlap 14 at 128^2 10.3 / 10.6; FP32 s = 12 at 512^2 10.3 / 9.7).
+template <typename T, int TX, int TY>
 struct FewShape {
     static constexpr int C = TX / 16, R = 2, W = TY / 8;
-    static constexpr bool ok = TX <= 64;  // interface rows of FP64 within the LDS
+    static constexpr bool ok = TX <= 64 && (TY <= 64 || sizeof(T) == 4);
 };
 
 }  // namespace
