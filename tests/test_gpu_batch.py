@@ -278,3 +278,24 @@ def test_batch_register_tiles_at_other_sweep_counts(orc, s, ov):
         assert infos[i].cycles == 5
         want = orc.hier_2d(f, np.zeros_like(f), hx, hy, (64, 64), s, 5, (ov, ov))
         assert np.array_equal(host(X), want), f"problem {i}"
+
+
+@pytest.mark.parametrize("side", [1, 8, 16, 17, 45, 46, 64])
+def test_judge_over_partial_counts(side):
+    """Problems of side^2 tiles, below, at and past one read of the judge's
+    workgroup (256) and one pass of it (2048): the residual and the stopping
+    cycle of the problem's own solve."""
+    n = 18 + 14 * side
+    rng = np.random.default_rng(side)
+    f = torch.as_tensor(rng.standard_normal((n, n)), device="cuda")
+    kw = dict(tile=(32, 32), s=10, overlap=(18, 18))
+    X = torch.zeros_like(f)
+    one = hj.solve_2d(f, X, 1.0 / (n + 1), rel_tol=0.02, max_cycles=60, allow_not_converged=True, **kw)
+    Y = [torch.zeros_like(f), torch.zeros_like(f)]
+    infos = hj.solve_batched([(f, y, 1.0 / (n + 1)) for y in Y], rel_tol=0.02, max_cycles=60,
+                             allow_not_converged=True, **kw)
+    for info, y in zip(infos, Y):
+        assert info.cycles == one.cycles and torch.equal(X, y)
+        # sums of the same partials in another order: at most 4096 of them
+        assert abs(info.rel_residual - one.rel_residual) <= 1e-12 * one.rel_residual
+        assert abs(info.r0_norm - one.r0_norm) <= 1e-12 * one.r0_norm
