@@ -15,8 +15,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libhj.so")
-SOURCES = ["hj_api.hip", "hj_kernels.hip", "hj_refine.hip", "hj_vc.hip", "hj_batch.hip", "hj_solve1d_wg.hip",
-           "hj_solve_vc_wg.hip"]
+SOURCES = ["hj_api.hip", "hj_kernels.hip", "hj_refine.hip", "hj_vc.hip", "hj_batch.hip", "hj_solve1d_wg.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -895,7 +895,7 @@ hj_status run_batch(const hj_problem *probs, int64_t nprob, hj_dtype dt, double 
 constexpr int64_t kWgChunk = 4096;
 
 // Solve every right-hand side in a workgroup of its own (see
-// hj_solve_vc_wg.hip): the iterates, cycle counts and infos of the paths
+// hj_solve_vc_wg.h): the iterates, cycle counts and infos of the paths
 // below.  A batch judges every iterate also without a tolerance, as
 // solve_vc_batched does (a right-hand side that is not finite stops there).
 hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const hj_params &P, hipStream_t st,

@@ -1,4 +1,4 @@
-// hj_solve_vc_wg.hip -- whole variable-coefficient solves, one workgroup per
+// hj_solve_vc_wg.h -- whole variable-coefficient solves, one workgroup per
 // right-hand side.
 //
 // A hierarchical cycle whose overlap reaches 2 s - 2 on each axis that has
@@ -11,6 +11,8 @@
 // between them.  The residual of the iterate a cycle starts from is formed in
 // its first sweep and judged before the next cycle, so the solve stops at the
 // same iterate as the per-cycle path.
+#pragma once
+
 #include "hj_launch.h"
 #include "hj_tiles.h"
 #include "hj_wg.h"
@@ -18,13 +20,13 @@
 namespace hj {
 namespace {
 
-constexpr int W = 8;  // most wavefronts of a workgroup
+constexpr int kVcWaves = 8;  // most wavefronts of a workgroup
 
 // Rows that wavefronts hand to each other, by sweep parity.
 struct VcWgLds {
-    double bot[2][W + 1][64];  // wavefront w's last row in [w + 1]; [0] is the boundary
-    double top[2][W + 1][64];  // wavefront w's first row in [w]; the one after the last is the boundary
-    double red[W];             // wavefront sums
+    double bot[2][kVcWaves + 1][64];  // wavefront w's last row in [w + 1]; [0] is the boundary
+    double top[2][kVcWaves + 1][64];  // wavefront w's first row in [w]; the one after the last is the boundary
+    double red[kVcWaves];             // wavefront sums
 };
 
 // The value of the lane CTRL selects, 0 where there is none.
@@ -110,7 +112,7 @@ __device__ __forceinline__ void solve_vc_body(const GeomVC &g, const double *__r
         L.bot[0][0][j] = L.bot[1][0][j] = 0.0;
         L.top[0][nw][j] = L.top[1][nw][j] = 0.0;
     }
-    if (threadIdx.x < W) L.red[threadIdx.x] = 0.0;
+    if (threadIdx.x < kVcWaves) L.red[threadIdx.x] = 0.0;
 
     // Rows beside the lane's, for the next sweep; par: the buffer they came
     // from.  A buffer is rewritten two sweeps later, after a barrier every
@@ -198,11 +200,11 @@ __device__ __forceinline__ void solve_vc_body(const GeomVC &g, const double *__r
         double tot = 0.0;
         const double mine = sweep.template operator()<true>(none, none);
         if (s > 1) {
-            sweep.template operator()<false>([&] { post(wave_sum63(mine)); }, [&] { tot = tree_sum<W>(L.red); });
+            sweep.template operator()<false>([&] { post(wave_sum63(mine)); }, [&] { tot = tree_sum<kVcWaves>(L.red); });
         } else {
             post(wave_sum63(mine));
             __syncthreads();
-            tot = tree_sum<W>(L.red);
+            tot = tree_sum<kVcWaves>(L.red);
         }
         // two sweeps a trip: they trade the rows' registers
         int it = 2;
@@ -230,7 +232,7 @@ __device__ __forceinline__ void solve_vc_body(const GeomVC &g, const double *__r
             point.template operator()<true>(i, x[i], i > 0 ? x[i - 1] : up, i < R - 1 ? x[i + 1] : dn, rsq);
         post(wave_sum63(rsq));
         __syncthreads();
-        J.take(maxc, tree_sum<W>(L.red));
+        J.take(maxc, tree_sum<kVcWaves>(L.red));
     }
     leave(c_sweep);
 }
@@ -238,7 +240,7 @@ __device__ __forceinline__ void solve_vc_body(const GeomVC &g, const double *__r
 // Workgroup b solves right-hand side b; launched with the wavefronts that hold
 // the grid's rows.
 template <int R, bool MASK>
-__global__ __launch_bounds__(64 * W) void k_solve_vc_wg(GeomVC g, const double *__restrict__ f,
+__global__ __launch_bounds__(64 * kVcWaves) void k_solve_vc_wg(GeomVC g, const double *__restrict__ f,
                                                          double *__restrict__ u, int64_t stride, int s,
                                                          int64_t c_begin, int64_t c_end, int64_t maxc, double tol,
                                                          int every, Ctrl *ctrls)
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(64 * W) void k_solve_vc_wg(GeomVC g, const double *
 }
 
 template <int R>
-hipError_t launch_t(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
+hipError_t launch_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
                     int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls, hipStream_t st)
 {
     const unsigned nw = (unsigned)(g.ny + R - 1) / R;
@@ -291,11 +293,11 @@ hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, in
         return launch(g, batch, stride, s, f, u, c_begin, c_end, maxc, tol, every, ctrls, st);
     };
     // rows a wavefront: the fewest that hold the grid in eight
-    if (g.ny <= 16) return at(launch_t<2>);
-    if (g.ny <= 24) return at(launch_t<3>);
-    if (g.ny <= 32) return at(launch_t<4>);
-    if (g.ny <= 48) return at(launch_t<6>);
-    return at(launch_t<8>);
+    if (g.ny <= 16) return at(launch_vc_wg<2>);
+    if (g.ny <= 24) return at(launch_vc_wg<3>);
+    if (g.ny <= 32) return at(launch_vc_wg<4>);
+    if (g.ny <= 48) return at(launch_vc_wg<6>);
+    return at(launch_vc_wg<8>);
 }
 
 }  // namespace hj

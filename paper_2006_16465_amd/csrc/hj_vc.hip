@@ -7,6 +7,7 @@
 
 #include "hj_launch.h"
 #include "hj_vc_tile.h"
+#include "hj_solve_vc_wg.h"
 
 namespace hj {
 namespace {
