@@ -908,6 +908,8 @@ hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const
     hj::Ctrl *ctrls = (hj::Ctrl *)B.wg;
     HJ_HIP(hj::launch_ctrl_init_n(ctrls, pr.batch, st));
     const int64_t maxc = P.max_cycles;
+    // at most 65 536 sweeps a launch (25 ms at 64 x 64), however long a cycle is
+    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(kWgChunk, 65536 / P.s));
     const bool judged = P.rel_tol > 0.0, every = judged || pr.batch > 1;
     std::vector<hj::Ctrl> hc((size_t)pr.batch);
     auto read_back = [&]() -> hj_status {
@@ -916,7 +918,7 @@ hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const
         return HJ_OK;
     };
     for (int64_t cb = 0;;) {
-        const int64_t ce = maxc - cb < kWgChunk ? maxc + 1 : cb + kWgChunk;
+        const int64_t ce = maxc - cb < chunk ? maxc + 1 : cb + chunk;
         HJ_HIP(hj::launch_solve_vc_wg(g, pr.batch, pr.batch > 1 ? pr.batch_stride : 0, P.s, f, u, cb, ce, maxc,
                                       judged ? P.rel_tol : -1.0, every, ctrls, st));
         if (ce == maxc + 1) break;

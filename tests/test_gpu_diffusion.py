@@ -385,3 +385,18 @@ def test_vc_one_workgroup_not_finite_and_long_runs(nx, ny):
                 out.append((st, host(U)))
             assert out[0][0] == out[1][0], name
             assert np.array_equal(out[0][1], out[1][1], equal_nan=True), name
+
+
+def test_vc_one_workgroup_long_cycles_match_oracle(orc):
+    """Cycles of more sweeps than a launch runs (one a launch), and of half as many."""
+    rng = np.random.default_rng(2)
+    a, f = np.exp(0.3 * rng.standard_normal((7, 8))), rng.standard_normal((2, 5, 6))
+    for s in (32768, 70000):
+        for tol in (0.0, 1e-100):
+            U = torch.zeros_like(dev(f))
+            hj.solve_vc_2d(dev(a), dev(f), U, hx=0.2, hy=0.3, tile=(16, 16), s=s, rel_tol=tol, max_cycles=3,
+                           allow_not_converged=True)
+            for b in range(2):
+                want, co = orc.vc_solve_2d(a, f[b], np.zeros((5, 6)), 0.2, 0.3, tile=(16, 16), s=s, tol=tol,
+                                           max_cycles=3)[:2]
+                assert np.array_equal(host(U)[b], want), (s, tol, b)
