@@ -251,53 +251,5 @@ __global__ __launch_bounds__(64 * kVcWaves) void k_solve_vc_wg(GeomVC g, const d
                                     ctrls + b, L);
 }
 
-template <int R>
-hipError_t launch_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
-                    int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls, hipStream_t st)
-{
-    const unsigned nw = (unsigned)(g.ny + R - 1) / R;
-    auto go = [&](auto kernel) -> hipError_t {
-        kernel<<<(unsigned)batch, 64 * nw, 0, st>>>(g, f, u, stride, s, c_begin, c_end, maxc, tol, every ? 1 : 0,
-                                                    ctrls);
-        return hipGetLastError();
-    };
-    if (g.nx == 64 && g.ny == (int)nw * R) return go(k_solve_vc_wg<R, false>);
-    return go(k_solve_vc_wg<R, true>);
-}
-
 }  // namespace
-
-// Grids of at most 64 x 64 points whose cycle is s sweeps of the whole grid.
-// There a sweep by one workgroup (0.38 us at 64 x 64) takes no longer than one
-// by the workgroup of a 64 x 64 tile, and the cycle's launch, its loads and
-// stores and the tiles' overlap fall away: us a cycle with a launch each and
-// here, s = 8, overlap 14: one right-hand side at 64 x 64 (64 x 32 tiles) 7.8
-// and 3.8, 16 of them 11.3 and 3.8, 1024 of them 48 and 17; four at 20 x 20
-// (32 x 32 tiles) 11.4 and 2.5; 1024 at 30 x 30 20 and 8.9.  Higher grids do
-// not fit a SIMD's registers with two wavefronts (64 x 128: 13.9 and 10.1 with
-// 16 right-hand sides, but slower with one), nor wider ones a row a wavefront.
-bool solve_vc_wg_supported(const GeomVC &g, int s)
-{
-    auto whole = [s](int tiles, int overlap) { return tiles == 1 || overlap >= 2 * ((int64_t)s - 1); };
-    return g.reg && g.nx <= 64 && g.ny <= 64 && whole(g.ntx, g.ox) && whole(g.nty, g.oy);
-}
-
-hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
-                              int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls,
-                              hipStream_t st)
-{
-    if (!solve_vc_wg_supported(g, s) || batch < 1 || batch > INT32_MAX || c_begin < 0 || c_end <= c_begin ||
-        c_end - 1 > maxc || s < 1)
-        return hipErrorInvalidValue;
-    auto at = [&](auto launch) {
-        return launch(g, batch, stride, s, f, u, c_begin, c_end, maxc, tol, every, ctrls, st);
-    };
-    // rows a wavefront: the fewest that hold the grid in eight
-    if (g.ny <= 16) return at(launch_vc_wg<2>);
-    if (g.ny <= 24) return at(launch_vc_wg<3>);
-    if (g.ny <= 32) return at(launch_vc_wg<4>);
-    if (g.ny <= 48) return at(launch_vc_wg<6>);
-    return at(launch_vc_wg<8>);
-}
-
 }  // namespace hj
