@@ -26,7 +26,10 @@ constexpr int kVcWaves = 8;  // most wavefronts of a workgroup
 struct VcWgLds {
     double bot[2][kVcWaves + 1][64];  // wavefront w's last row in [w + 1]; [0] is the boundary
     double top[2][kVcWaves + 1][64];  // wavefront w's first row in [w]; the one after the last is the boundary
-    double red[kVcWaves];             // wavefront sums
+    // Wavefront sums of one iterate's residual.  There is one set: between its
+    // reading and the next posting every path has a barrier, of a sweep (the
+    // first of the next cycle) or before the last iterate's residual.
+    double red[kVcWaves];
 };
 
 // The value of the lane CTRL selects, 0 where there is none.
@@ -226,6 +229,9 @@ __device__ __forceinline__ void solve_vc_body(const GeomVC &g, const double *__r
     }
     store();
     if (c_end == maxc + 1) {
+        // with s <= 2 no barrier has followed the reading of iterate maxc - 1's
+        // sums: a wavefront that posted now would change them under a later one
+        __syncthreads();
         double rsq = 0.0;
 #pragma unroll
         for (int i = 0; i < R; ++i)
