@@ -519,16 +519,18 @@ def _vc_problem(a, f, hx, hy):
 
 def solve_vc_2d(a, f, u, h=None, *, hx=None, hy=None, tile=(32, 32), s=8, overlap=(0, 0),
                 method="hierarchical", rel_tol=1e-10, max_cycles=1_000_000, check_every=0,
-                allow_not_converged=False, lds_kernel=False):
+                allow_not_converged=False, lds_kernel=False, launch_per_cycle=False):
     """Solve -div(a grad u_b) = f_b for a batch (hj_solve_vc_2d); u (same shape as f) in/out.
-    Returns one Info per right-hand side.  lds_kernel: HJ_FLAG_LDS_KERNEL."""
+    Returns one Info per right-hand side.  lds_kernel: HJ_FLAG_LDS_KERNEL; launch_per_cycle:
+    HJ_FLAG_LAUNCH_PER_CYCLE, small solves by the tile kernels too (same iterates)."""
     _check_pair(f, u)
     hx = hx if hx is not None else h
     hy = hy if hy is not None else hx
     pr = _vc_problem(a, f, hx, hy)
     if not u.is_contiguous():
         raise ValueError("u must be contiguous")
-    p = make_params(tile, s, method, rel_tol, max_cycles, check_every, overlap, lds_kernel=lds_kernel)
+    p = make_params(tile, s, method, rel_tol, max_cycles, check_every, overlap, lds_kernel=lds_kernel,
+                    launch_per_cycle=launch_per_cycle)
     infos = (_Info * pr.batch)()
     with _device(f):
         st = load().hj_solve_vc_2d(ctypes.byref(pr), f.data_ptr(), u.data_ptr(), ctypes.byref(p),
@@ -558,13 +560,13 @@ def vc_grad_a(a, u, lam, h=None, *, hx=None, hy=None):
 
 def solve_adjoint(a, u, dl_du, lam, h=None, *, hx=None, hy=None, tile=(32, 32), s=8, overlap=(0, 0),
                   method="hierarchical", rel_tol=1e-10, max_cycles=1_000_000, check_every=0, grad_a=True,
-                  allow_not_converged=False):
+                  allow_not_converged=False, launch_per_cycle=False):
     """Backward pass of the variable-coefficient solve (hj_solve_adjoint): solves
     A(a) lam_b = dL/du_b in place in lam (lam holds the initial guess on entry;
     A is symmetric, so this is the forward solve on dL/du), which is dL/df, and,
     with grad_a, dL/da from the forward states u and lam summed over the batch.
     u, dl_du, lam: (ny, nx) or (batch, ny, nx) contiguous FP64; a: (ny+2, nx+2).
-    Returns (infos, dl_da or None)."""
+    launch_per_cycle: as in solve_vc_2d.  Returns (infos, dl_da or None)."""
     import torch
     hx = hx if hx is not None else h
     hy = hy if hy is not None else hx
@@ -582,7 +584,8 @@ def solve_adjoint(a, u, dl_du, lam, h=None, *, hx=None, hy=None, tile=(32, 32), 
     grad = torch.empty_like(a) if grad_a else None
     d.dl_da = grad.data_ptr() if grad_a else None
     d.ld_grad = a.shape[1]
-    d.params = make_params(tile, s, method, rel_tol, max_cycles, check_every, overlap)
+    d.params = make_params(tile, s, method, rel_tol, max_cycles, check_every, overlap,
+                           launch_per_cycle=launch_per_cycle)
     infos = (_Info * pr.batch)()
     with _device(dl_du):
         st = load().hj_solve_adjoint(ctypes.byref(d), _stream(dl_du), infos)

@@ -400,3 +400,48 @@ def test_vc_one_workgroup_long_cycles_match_oracle(orc):
                 want, co = orc.vc_solve_2d(a, f[b], np.zeros((5, 6)), 0.2, 0.3, tile=(16, 16), s=s, tol=tol,
                                            max_cycles=3)[:2]
                 assert np.array_equal(host(U)[b], want), (s, tol, b)
+
+
+# solves that would run whole in one workgroup (at most 64 x 64 points, overlaps
+# that reach 2 s - 2): by the tile kernels, the single solves' and the batched
+# engine's, register body and LDS body, and in one workgroup
+@pytest.mark.parametrize("n,tile,s,ov", [((64, 48), (16, 32), 6, (10, 10)), ((64, 48), (16, 16), 4, (6, 6)),
+                                         ((64, 48), (64, 32), 8, (14, 14)), ((64, 64), (64, 64), 3, (0, 0)),
+                                         ((40, 64), (64, 32), 1, (2, 2)), ((33, 47), (32, 32), 2, (5, 3)),
+                                         ((20, 24), (16, 16), 6, (10, 10)), ((1, 1), (16, 16), 1, (0, 0))])
+def test_vc_small_solves_by_every_path_match_oracle(orc, n, tile, s, ov):
+    nx, ny = n
+    hx, hy = 1.0 / (nx + 1), 0.9 / (ny + 1)
+    rng = np.random.default_rng(nx + 100 * ny + s)
+    a = np.exp(0.5 * rng.standard_normal((ny + 2, nx + 2)))
+    f, u0 = rng.standard_normal((3, ny, nx)), rng.standard_normal((3, ny, nx))
+    kw = dict(tile=tile, s=s, overlap=ov)
+    say(f"vc small by every path {n} {tile} s={s}")
+    for tol, cap in ((0.0, 3), (1e-100, 4), (0.3, 10_000)):
+        want = [orc.vc_solve_2d(a, f[b], u0[b], hx, hy, tol=tol, max_cycles=cap, **kw) for b in range(3)]
+        for nb in (1, 3):
+            for path in ({}, {"launch_per_cycle": True}, {"lds_kernel": True}):
+                U = dev(u0[:nb])
+                infos = hj.solve_vc_2d(dev(a), dev(f[:nb]), U, hx=hx, hy=hy, rel_tol=tol, max_cycles=cap,
+                                       allow_not_converged=True, **path, **kw)
+                for b, (xo, co, relo, r0o) in enumerate(want[:nb]):
+                    assert np.array_equal(host(U)[b], xo), (tol, nb, path, b)
+                    assert infos[b].cycles == (co if co >= 0 else cap), (tol, nb, path, b)
+                    # sums of at most 4096 squares in another order: 4096 x 2^-53 of each, on either side
+                    assert abs(infos[b].r0_norm - r0o) <= 1e-12 * r0o
+                    assert abs(infos[b].rel_residual - relo) <= 2e-12 * relo
+
+
+def test_adjoint_by_every_path_is_the_same():
+    rng = np.random.default_rng(9)
+    nx, ny = 50, 41
+    a = dev(np.exp(0.5 * rng.standard_normal((ny + 2, nx + 2))))
+    u, g = dev(rng.standard_normal((3, ny, nx))), dev(rng.standard_normal((3, ny, nx)))
+    out = []
+    for per_cycle in (False, True):
+        lam = torch.zeros_like(g)
+        infos, grad = hj.solve_adjoint(a, u, g, lam, 1.0 / 51, tile=(32, 32), s=5, overlap=(8, 9), rel_tol=1e-6,
+                                       launch_per_cycle=per_cycle)
+        out.append(([i.cycles for i in infos], lam, grad))
+    assert out[0][0] == out[1][0]
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
