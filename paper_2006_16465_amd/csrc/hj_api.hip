@@ -343,7 +343,9 @@ constexpr const char *kNeedFullTile =
     "tiles with a 128 extent run only in the register kernel, on grids of at least one full tile "
     "(nx >= tile_x, ny >= tile_y, no HJ_FLAG_LDS_KERNEL)";
 
-hj::Geom2 make_geom2(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, const hj_params &p)
+// dt: the precision of the cycles (it decides the order of the tiles only)
+hj::Geom2 make_geom2(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, const hj_params &p,
+                     hj_dtype dt = HJ_F64)
 {
     hj::Geom2 g;
     g.nx = (int)nx;
@@ -355,7 +357,10 @@ hj::Geom2 make_geom2(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, c
     g.oy = p.overlap_y;
     g.ntx = hj::axis_count(g.nx, g.tx, g.ox);
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
-    g.walk = hj::make_walk(g.ntx, g.nty, 24 * (int64_t)g.tx * g.ty);
+    const int64_t tile_bytes = 24 * (int64_t)g.tx * g.ty;
+    // in double: the products of the largest accepted axes leave 64 bits
+    const double moved = dt == HJ_F64 ? (double)g.ntx * g.nty * tile_bytes : 12.0 * nx * ny;
+    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, moved > hj::kLargeBytes);
     g.iso = hx == hy;
     g.reg = (p.flags & HJ_FLAG_LDS_KERNEL) ? 0 : 1;
     g.hh = hx * hx;
@@ -406,7 +411,8 @@ hj::GeomVC make_geom_vc(const hj_vc_problem &pr, const hj_params &p)
     g.oy = p.overlap_y;
     g.ntx = hj::axis_count(g.nx, g.tx, g.ox);
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
-    g.walk = hj::make_walk(g.ntx, g.nty, 32 * (int64_t)g.tx * g.ty);
+    const int64_t tile_bytes = 32 * (int64_t)g.tx * g.ty;
+    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, (double)g.ntx * g.nty * tile_bytes > hj::kLargeBytes);
     g.a = pr.a;
     g.lda = pr.lda;
     g.ihx2 = 1.0 / (pr.hx * pr.hx);
@@ -518,7 +524,7 @@ hj_status time_shape(int dim, int64_t nx, int64_t ny, hj_dtype dt, const hj_para
     hj::Geom2 g2{};
     hj::Geom1 g1{};
     if (dim == 2) {
-        g2 = make_geom2(nx, ny, nx, h, h, P);
+        g2 = make_geom2(nx, ny, nx, h, h, P, dt);
         if (!g2.reg || nx < g2.tx || ny < g2.ty) {
             us = -1.0;
             return HJ_OK;
@@ -714,7 +720,7 @@ hj_status run_batch(const hj_problem *probs, int64_t nprob, hj_dtype dt, double 
         b.x = q.x;
         int64_t elems = 0;
         if (q.dim == 2) {
-            b.g2 = make_geom2(q.nx, q.ny, q.ld, q.hx, q.hy, P2);
+            b.g2 = make_geom2(q.nx, q.ny, q.ld, q.hx, q.hy, P2, dt);
             b.nitems = (int64_t)b.g2.ntx * b.g2.nty;
             b.s = P2.s;
             elems = q.ny * q.ld;
@@ -1038,7 +1044,7 @@ hj_status solve_2d_on(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, 
                       const void *f, void *x, const hj_params &P, hipStream_t st, void *xs,
                       const Ctl &K, hj_info *info)
 {
-    const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P);
+    const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P, dtype);
     const int dt = dtype == HJ_F64 ? hj::F64 : hj::F32;
     const size_t es = esize(dtype);
     const bool hier = P.method == HJ_HIERARCHICAL;
@@ -1194,7 +1200,8 @@ hj_status hj_solve_2d_refined(int64_t nx, int64_t ny, int64_t ld, double hx, dou
     DevScratch &S = g_scr[dev];
     std::lock_guard<std::mutex> lock(S.mu);
     const hj_params P = p->inner;
-    const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P);
+    const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P);            // of the FP64 cycles
+    const hj::Geom2 g32 = make_geom2(nx, ny, ld, hx, hy, P, HJ_F32);  // of the FP32 ones
     const bool hier = P.method == HJ_HIERARCHICAL;
     const int64_t nbc = hier ? hj::cycle2d_blocks(g) : hj::sweep2d_blocks(g);
     const int64_t nbr = hj::resid2d_blocks(g);
@@ -1213,7 +1220,7 @@ hj_status hj_solve_2d_refined(int64_t nx, int64_t ny, int64_t ld, double hx, dou
     step.nb_cycle = (int)nbc;
     step.nb_resid = (int)nbr;
     step.cycle = [&](const void *xi, void *xo, bool res, double tol, const hj::Red &red) {
-        return hier ? hj::launch_cycle2d(hj::F32, g, P.s, res, r32, xi, xo, red, tol, st)
+        return hier ? hj::launch_cycle2d(hj::F32, g32, P.s, res, r32, xi, xo, red, tol, st)
                     : hj::launch_sweep2d(hj::F32, g, res, r32, xi, xo, red, tol, st);
     };
     step.resid = [&](const void *xi, double *part) {
@@ -1599,7 +1606,7 @@ hj_status hj_autotune_solve(int64_t nx, int64_t ny, int64_t ld, double hx, doubl
     };
     // time per cycle from a few fixed cycles between the spare arrays
     auto cycle_ms = [&](const hj_params &P, double &ms) -> hj_status {
-        const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P);
+        const hj::Geom2 g = make_geom2(nx, ny, ld, hx, hy, P, dtype);
         const hj::Red none{nullptr, nullptr, S.ctrl, 0, 0};
         void *a = xs, *b = (char *)xs + xbytes;
         HJ_HIP(hj::launch_cycle2d(dt, g, P.s, false, f, a, b, none, -1.0, st));

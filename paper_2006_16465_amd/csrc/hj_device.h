@@ -95,19 +95,28 @@ struct Walk {
     FastDiv last;   // tile columns of the last strip
 };
 
-// Strips of equal width whose row of tiles moves at most kStripBytes.  An XCD
-// works on a contiguous run of the walk, about 64 tiles at a time, so the
-// overlap (or halo) rows that vertical neighbours share are read again while
-// its 4 MB L2 still holds them; row by row over the whole grid they come back
-// after tiles_x tiles.  Measured at 4096^2, us per FP64 cycle, whole rows /
-// strips: 32 x 32 tiles 97 / 90 (3.1 MB a row; strips of 16, 24 and 43 columns
-// alike), 64 x 64 o = 22 138 / 136, 64 x 128 o = 22 147 / 145.  Grids whose
-// tiles move less than the memory-side cache holds (kLargeBytes) keep whole
-// rows: FP32 2049 x 1531, 64 x 64, 17.9 / 18.1.
-inline Walk make_walk(int ntx, int nty, int64_t tile_bytes)
+// Strips of equal width whose row of tiles moves at most kStripBytes (large:
+// the grid is one to be walked in strips).  An XCD works on a contiguous run of
+// the walk, about 64 tiles at a time, so the overlap (or halo) rows that
+// vertical neighbours share are read again while its 4 MB L2 still holds them;
+// row by row over the whole grid they come back after tiles_x tiles.  Measured
+// at 4096^2, us per FP64 cycle, whole rows / strips: 32 x 32 tiles 97 / 90
+// (3.1 MB a row; strips of 16, 24 and 43 columns alike), 64 x 64 o = 22
+// 138 / 136, 64 x 128 o = 22 147 / 145.
+//
+// FP64 grids are large where their tiles move more than the memory-side cache
+// holds (kLargeBytes), the parts that overlap counted each time: 3000^2, 32 x 32,
+// s = 4, overlap 6 (330 MB of tiles, 216 MB of grid), without residual 47 / 42 us.
+// FP32 grids where the grid itself does: at 4096^2 (201 MB of grid), 32 x 32
+// tiles, s = 4, overlap 6 (306 MB of tiles) 44.0 / 46.5, s = 2, overlap 2
+// 39.3 / 41.7, other shapes alike; beyond, s = 4, 5200^2 105.6 / 103.5, 6500^2
+// 166.7 / 161.6.  Strips are as wide for FP32 as for FP64 (tile_bytes of
+// FP64 points): twice as wide they took 2 % more at 6000^2, s = 2 and 4.
+constexpr double kLargeBytes = 256 << 20;
+
+inline Walk make_walk(int ntx, int nty, int64_t tile_bytes, bool large)
 {
-    constexpr int64_t kStripBytes = 3 << 19, kLargeBytes = 256 << 20;
-    const bool large = (int64_t)ntx * nty * tile_bytes > kLargeBytes;
+    constexpr int64_t kStripBytes = 3 << 19;
     const int64_t most = large ? kStripBytes / tile_bytes : ntx;
     const int cap = most < 1 ? 1 : most > ntx ? ntx : (int)most;
     const int strips = (ntx + cap - 1) / cap;

@@ -672,3 +672,15 @@ def test_stop_is_the_same_however_often_the_host_looks(orc, method):
             info = solve(dev(f), X, rel_tol=tol, max_cycles=cap, check_every=every, **kw)
             assert info.cycles == want and info.status == hj.HJ_OK, (want, every, cap)
             assert np.array_equal(host(X), ref), (want, every, cap)
+
+
+@pytest.mark.parametrize("n,tile,ov", [((4600, 4601), (32, 32), (6, 2)), ((5003, 4999), (32, 32), (2, 6)),
+                                       ((2602, 9001), (64, 128), (22, 22))])
+def test_fp32_walk_on_both_sides_of_the_strip_rule(orc, n, tile, ov):
+    """FP32 grids just below and above the size from which they are walked in strips."""
+    nx, ny = n
+    f, x0 = W.rhs_random((ny, nx), 41), W.rhs_random((ny, nx), 42)
+    h = 1.0 / (nx + 1)
+    say(f"fp32 walk {n} {tile} {ov}")
+    got, _ = gpu_cycles_2d(f, x0, h, tile, 2, 2, ov, dtype=torch.float32)
+    assert np.array_equal(got, orc.hier_2d_f32(f, x0, h, h, tile, 2, 2, ov))
