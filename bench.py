@@ -83,7 +83,8 @@ def sweep_bytes_per_launch(n, esize=8):
 def cycle_kernel_name(tile, n):
     """Name of the cycle kernel the library runs for this tile on an n x n
     grid of many tiles: register-resident tiles of C = tx/16 columns and 4 rows
-    per lane over W wavefronts, else the LDS kernel."""
+    per lane over W wavefronts (32 x 128, no row's tile here, has 8 on large
+    grids), else the LDS kernel."""
     tx, ty = tile
     if tx in (32, 64, 128) and ty in (16, 32, 64, 128) and n >= max(tile):
         return f"k_cycle2d_reg<double,{tx // 16},4,{ty // 16},true,true,false>"

@@ -305,6 +305,11 @@ hipError_t cyc2(const Geom2 &g, int s, bool res, const void *f, const void *xin,
                 if ((int64_t)g.ntx * g.nty * S::W <= kSimds)
                     return cyc2_reg<T, F::C, F::R, F::W, true>(g, s, res, f, xin, xout, red, tol, st);
             }
+            using M = ManyShape<T, TX, TY>;
+            if constexpr (M::ok) {
+                if ((int64_t)g.ntx * g.nty >= kManyTiles)
+                    return cyc2_reg<T, M::C, M::R, M::W, false>(g, s, res, f, xin, xout, red, tol, st);
+            }
             return cyc2_reg<T, S::C, S::R, S::W, false>(g, s, res, f, xin, xout, red, tol, st);
         }
     }

@@ -637,10 +637,10 @@ __device__ __forceinline__ double tiles_1d(const Geom1 &g, int64_t blk, const T 
 // Register-resident shape for a TX x TY tile: C columns and R = 4 rows per
 // lane, W wavefronts.  Eight rows a lane (32 x 32 and 64 x 32 on one
 // wavefront, 32 x 64 on two) move half the interface rows but hold twice the
-// registers: us per cycle, eight rows / four, FP64 1024^2 64 x 32 s = 8 o = 14
-// 14.3 / 12.4, 32 x 64 s = 32 o = 8 21.3 / 19.3, FP32 2048^2 32 x 64 41.7 /
-// 36.9; equal within 2 % for 32 x 32 on larger grids, 124 / 130 at worst
-// (FP64 4096^2 64 x 32).
+// registers: us per cycle with residual, eight rows / four, FP64 64 x 32 s = 8
+// o = 14 at 1024^2 14.1 / 12.2, at 4096^2 121.9 / 119.9, 32 x 64 s = 32 o = 8
+// at 1024^2 21.3 / 19.8, FP32 at 2048^2 41.9 / 37.2; 32 x 32 within 2 % but for
+// FP32 s = 8 o = 14 at 4096^2 (87.5 / 90.9) and at 1024^2 (11.9 / 10.8).
 template <int TX, int TY>
 struct RegShape {
     static constexpr int C = TX / 16;
@@ -648,6 +648,19 @@ struct RegShape {
     static constexpr int W = TY / (4 * R);
     static constexpr bool ok = (TX == 32 || TX == 64 || TX == 128) && TY >= 16 && TY <= 128 &&
                                W >= 1 && 4 * R * W == TY;
+};
+
+// Shape for grids of many tiles: eight rows a lane on four wavefronts, for FP64
+// 32 x 128 tiles from kManyTiles on (us per cycle, s = 24, overlap 22, four
+// rows / eight: 4096^2 355.7 / 336.2, 2048^2 86.7 / 83.7; s = 8, overlap 14
+// 2048^2, the line, 28.6 / 28.8; below it 1500^2 19.2 / 19.6, 700^2 10.2 /
+// 10.4).  FP32 is 2 to 4 % slower so (s = 24, 2048^2 60.0 / 62.2).
+constexpr int64_t kManyTiles = 2048;
+
+template <typename T, int TX, int TY>
+struct ManyShape {
+    static constexpr int C = TX / 16, R = 8, W = TY / 32;
+    static constexpr bool ok = TX == 32 && TY == 128 && sizeof(T) == 8;
 };
 
 // Shape for grids of few tiles: two rows a lane, so that a tile's sweep runs on

@@ -684,3 +684,21 @@ def test_fp32_walk_on_both_sides_of_the_strip_rule(orc, n, tile, ov):
     say(f"fp32 walk {n} {tile} {ov}")
     got, _ = gpu_cycles_2d(f, x0, h, tile, 2, 2, ov, dtype=torch.float32)
     assert np.array_equal(got, orc.hier_2d_f32(f, x0, h, h, tile, 2, 2, ov))
+
+
+@pytest.mark.parametrize("n", [(32 * 64, 128 * 32), (32 * 63 - 5, 128 * 32 - 3), (32 * 63, 128 * 32)])
+@pytest.mark.parametrize("iso", [True, False])
+def test_many_tiles_shape_matches_oracle(orc, n, iso):
+    """FP64 32 x 128 tiles on both sides of 2048 of them (2048, 2016 and 2016), with and without residual."""
+    nx, ny = n
+    f, x0 = W.rhs_random((ny, nx), 51), W.rhs_random((ny, nx), 52)
+    hx = 1.0 / (nx + 1)
+    hy = hx if iso else 1.3 * hx
+    for s, ov in ((1, (0, 0)), (4, (3, 6)), (5, (0, 0))):
+        say(f"many tiles {n} iso={iso} s={s}")
+        want = orc.hier_2d(f, x0, hx, hy, (32, 128), s, 2, ov)
+        for tol in (0.0, 1e-100):
+            X = dev(x0)
+            hj.solve_2d(dev(f), X, hx=hx, hy=hy, tile=(32, 128), s=s, overlap=ov, rel_tol=tol, max_cycles=2,
+                        allow_not_converged=True)
+            assert np.array_equal(host(X), want), (s, ov, tol)
