@@ -914,8 +914,14 @@ hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const
     hj::Ctrl *ctrls = (hj::Ctrl *)B.wg;
     HJ_HIP(hj::launch_ctrl_init_n(ctrls, pr.batch, st));
     const int64_t maxc = P.max_cycles;
-    // at most 65 536 sweeps a launch (25 ms at 64 x 64), however long a cycle is
-    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(kWgChunk, 65536 / P.s));
+    // A launch takes at most 2^16 right-hand sides (2^25 threads: the count of
+    // a launch's threads is 32 bits wide and wraps without an error, at 2^23
+    // right-hand sides of 512) and runs at most 65 536 sweeps of up to 1 024 of
+    // them, fewer of more, but a whole cycle: 25 ms at 64 x 64 while all are
+    // resident (512 of them), 140 ms at 1 024 and above.
+    const int64_t slice = std::min<int64_t>(pr.batch, 65536);
+    const int64_t sweeps = 65536 * 1024 / std::max<int64_t>(slice, 1024);
+    const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(kWgChunk, sweeps / P.s));
     const bool judged = P.rel_tol > 0.0, every = judged || pr.batch > 1;
     std::vector<hj::Ctrl> hc((size_t)pr.batch);
     auto read_back = [&]() -> hj_status {
@@ -925,8 +931,10 @@ hj_status solve_vc_wg(const hj_vc_problem &pr, const double *f, double *u, const
     };
     for (int64_t cb = 0;;) {
         const int64_t ce = maxc - cb < chunk ? maxc + 1 : cb + chunk;
-        HJ_HIP(hj::launch_solve_vc_wg(g, pr.batch, pr.batch > 1 ? pr.batch_stride : 0, P.s, f, u, cb, ce, maxc,
-                                      judged ? P.rel_tol : -1.0, every, ctrls, st));
+        for (int64_t b = 0; b < pr.batch; b += slice)
+            HJ_HIP(hj::launch_solve_vc_wg(g, std::min(slice, pr.batch - b), pr.batch_stride, P.s, f + b * pr.batch_stride,
+                                          u + b * pr.batch_stride, cb, ce, maxc, judged ? P.rel_tol : -1.0, every,
+                                          ctrls + b, st));
         if (ce == maxc + 1) break;
         if (every) {
             if ((r = read_back()) != HJ_OK) return r;

@@ -180,7 +180,7 @@ hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, in
                               int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls,
                               hipStream_t st)
 {
-    if (!solve_vc_wg_supported(g, s) || batch < 1 || batch > INT32_MAX || c_begin < 0 || c_end <= c_begin ||
+    if (!solve_vc_wg_supported(g, s) || batch < 1 || batch > 1 << 22 || c_begin < 0 || c_end <= c_begin ||
         c_end - 1 > maxc || s < 1)
         return hipErrorInvalidValue;
     auto at = [&](auto launch) {

@@ -445,3 +445,32 @@ def test_adjoint_by_every_path_is_the_same():
         out.append(([i.cycles for i in infos], lam, grad))
     assert out[0][0] == out[1][0]
     assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
+
+
+def _one_column(a, f, u, hy, sweeps):
+    """Jacobi sweeps of every 1-wide column of u at once (a shared), in the kernels' order of operations."""
+    ihx2, ihy2 = 1.0 / 0.25, 1.0 / (hy * hy)
+    c = a[1:-1, 1]
+    w, e = 0.5 * (c + a[1:-1, 0]) * ihx2, 0.5 * (c + a[1:-1, 2]) * ihx2
+    s, n = 0.5 * (c + a[:-2, 1]) * ihy2, 0.5 * (c + a[2:, 1]) * ihy2
+    dinv = 1.0 / ((w + e) + (s + n))
+    for _ in range(sweeps):
+        p = torch.nn.functional.pad(u, (1, 1))
+        u = (f + (s * p[:, :-2] + n * p[:, 2:])) * dinv
+    return u
+
+
+@pytest.mark.parametrize("nb", [65535, 65536, 65537, (1 << 23) + 3])
+def test_vc_one_workgroup_solves_of_very_many_right_hand_sides(nb):
+    """One launch's worth of right-hand sides, one more, and more than 2^32 threads hold."""
+    ny, cycles, s = 16, 2, 3
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.rand(ny + 2, 3, dtype=torch.float64, device="cuda", generator=gen) + 0.5
+    f = torch.randn(nb, ny, dtype=torch.float64, device="cuda", generator=gen)
+    u = torch.zeros_like(f)
+    say(f"vc one workgroup x {nb}")
+    pr = hj._vc_problem(a, f.reshape(nb, ny, 1), 0.5, 0.1)
+    p = hj.make_params((16, 16), s, rel_tol=0.0, max_cycles=cycles)
+    st = hj.load().hj_solve_vc_2d(ctypes.byref(pr), f.data_ptr(), u.data_ptr(), ctypes.byref(p), hj._stream(f), None)
+    assert st == hj.HJ_OK, hj.last_error()
+    assert torch.equal(u, _one_column(a, f, torch.zeros_like(f), 0.1, s * cycles))
