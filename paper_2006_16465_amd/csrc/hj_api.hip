@@ -1919,7 +1919,7 @@ hj_status hj_solve_vc_2d(const hj_vc_problem *prob, const double *f, double *u, 
     if (p->method == HJ_HIERARCHICAL && !(p->flags & HJ_FLAG_LAUNCH_PER_CYCLE) &&
         hj::solve_vc_wg_supported(make_geom_vc(*prob, *p), p->s))
         return solve_vc_wg(*prob, f, u, *p, (hipStream_t)stream, g_bat[dev], infos);
-    if (p->method == HJ_HIERARCHICAL && prob->batch > 1)
+    if (p->method == HJ_HIERARCHICAL && (prob->batch > 1 || !hj::cycle_vc_one_launch(make_geom_vc(*prob, *p))))
         return solve_vc_batched(*prob, f, u, *p, (hipStream_t)stream, dev, S, infos);
     return solve_vc_locked(*prob, f, u, *p, (hipStream_t)stream, S, infos);
 }

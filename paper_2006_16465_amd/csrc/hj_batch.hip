@@ -93,12 +93,11 @@ template <int M, int C, int R, int W, bool ISO>
 __global__ __launch_bounds__(64 * W, (min_waves_2d<std::conditional_t<M == BM_F32, float, double>, C, R>()))
 void k_batch_cycle2d(const BProb *__restrict__ probs,
                                                           const int32_t *__restrict__ owner,
-                                                          int64_t nitems, const BState *__restrict__ state,
+                                                          int64_t first, const BState *__restrict__ state,
                                                           double *part, int s)
 {
     constexpr int NT = 64 * W;
-    const int64_t w = xcd_tile(blockIdx.x, gridDim.x);
-    if (w >= nitems) return;
+    const int64_t w = first + xcd_tile(blockIdx.x, gridDim.x);
     const int p = owner[w];
     const BState &S = state[p];
     if (S.status != ST_RUNNING) return;
@@ -138,11 +137,10 @@ void k_batch_cycle2d(const BProb *__restrict__ probs,
 template <int M, int TT>
 __global__ __launch_bounds__(kNT) void k_batch_cycle1d(const BProb *__restrict__ probs,
                                                        const int32_t *__restrict__ owner,
-                                                       int64_t nitems, const BState *__restrict__ state,
+                                                       int64_t first, const BState *__restrict__ state,
                                                        double *part, int s)
 {
-    const int64_t w = xcd_tile(blockIdx.x, gridDim.x);
-    if (w >= nitems) return;
+    const int64_t w = first + xcd_tile(blockIdx.x, gridDim.x);
     const int p = owner[w];
     const BState &S = state[p];
     if (S.status != ST_RUNNING) return;
@@ -174,11 +172,10 @@ __global__ __launch_bounds__(kNT) void k_batch_cycle1d(const BProb *__restrict__
 // the single-problem kernel (hj_vc_tile.h).
 template <int TX, int TY, bool REG>
 __global__ __launch_bounds__((vc_threads<TX, TY>()), (vc_min_waves<TX, REG>())) void k_batch_cycle_vc(const BProb *__restrict__ probs,
-                                                        const int32_t *__restrict__ owner, int64_t nitems,
+                                                        const int32_t *__restrict__ owner, int64_t first,
                                                         const BState *__restrict__ state, double *part, int s)
 {
-    const int64_t w = xcd_tile(blockIdx.x, gridDim.x);
-    if (w >= nitems) return;
+    const int64_t w = first + xcd_tile(blockIdx.x, gridDim.x);
     const int p = owner[w];
     const BState &S = state[p];
     if (S.status != ST_RUNNING) return;
@@ -481,17 +478,20 @@ template <int M, int TX, int TY, bool ISO>
 hipError_t bcyc2(const BatchLaunch &L, hipStream_t st)
 {
     using S = RegShape<TX, TY>;
-    k_batch_cycle2d<M, S::C, S::R, S::W, ISO><<<(unsigned)L.nitems, 64 * S::W, 0, st>>>(
-        L.probs, L.owner, L.nitems, L.state, L.part, L.s);
-    return hipGetLastError();
+    return in_launches(L.nitems, 64 * S::W, [&](int64_t first, int64_t n) {
+        k_batch_cycle2d<M, S::C, S::R, S::W, ISO><<<(unsigned)n, 64 * S::W, 0, st>>>(L.probs, L.owner, first, L.state,
+                                                                                     L.part, L.s);
+        return hipGetLastError();
+    });
 }
 
 template <int M, int TT>
 hipError_t bcyc1(const BatchLaunch &L, hipStream_t st)
 {
-    k_batch_cycle1d<M, TT><<<(unsigned)L.nitems, kNT, 0, st>>>(L.probs, L.owner, L.nitems, L.state, L.part,
-                                                               L.s);
-    return hipGetLastError();
+    return in_launches(L.nitems, kNT, [&](int64_t first, int64_t n) {
+        k_batch_cycle1d<M, TT><<<(unsigned)n, kNT, 0, st>>>(L.probs, L.owner, first, L.state, L.part, L.s);
+        return hipGetLastError();
+    });
 }
 
 #define HJ_BATCH_TILES2(X) X(32, 16) X(32, 32) X(32, 64) X(32, 128) X(64, 16) X(64, 32) X(64, 64) X(64, 128)
@@ -523,9 +523,11 @@ hipError_t bcyc1_m(int t, const BatchLaunch &L, hipStream_t st)
 template <int TX, int TY, bool REG>
 hipError_t bcycvc(const BatchLaunch &L, hipStream_t st)
 {
-    k_batch_cycle_vc<TX, TY, REG><<<(unsigned)L.nitems, vc_threads<TX, TY>(), 0, st>>>(L.probs, L.owner, L.nitems,
-                                                                                  L.state, L.part, L.s);
-    return hipGetLastError();
+    return in_launches(L.nitems, vc_threads<TX, TY>(), [&](int64_t first, int64_t n) {
+        k_batch_cycle_vc<TX, TY, REG><<<(unsigned)n, vc_threads<TX, TY>(), 0, st>>>(L.probs, L.owner, first, L.state,
+                                                                                    L.part, L.s);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace
@@ -583,8 +585,10 @@ hipError_t launch_batch_cycle1d(int dt, bool refine, int t, const BatchLaunch &L
 hipError_t launch_batch_judge(const BProb *probs, int nprob, BState *state, const double *part,
                               const BRefine &rf, hipStream_t st)
 {
-    k_batch_judge<<<(unsigned)nprob, 256, 0, st>>>(probs, state, part, rf);
-    return hipGetLastError();
+    return in_launches(nprob, 256, [&](int64_t first, int64_t n) {
+        k_batch_judge<<<(unsigned)n, 256, 0, st>>>(probs + first, state + first, part, rf);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_batch_init(BState *state, int nprob, hipStream_t st)
@@ -596,9 +600,10 @@ hipError_t launch_batch_init(BState *state, int nprob, hipStream_t st)
 
 hipError_t launch_batch_finalize(const BProb *probs, int nprob, const BState *state, hipStream_t st)
 {
-    const dim3 grid((unsigned)nprob, 16);
-    k_batch_finalize<<<grid, 256, 0, st>>>(probs, state);
-    return hipGetLastError();
+    return in_launches(nprob, 256, [&](int64_t first, int64_t n) {
+        k_batch_finalize<<<dim3((unsigned)n, 16), 256, 0, st>>>(probs + first, state + first);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace hj

@@ -269,6 +269,7 @@ struct Red {
     Ctrl *ctrl;
     int64_t c;                // index of the iterate this kernel evaluates
     int nb_prev;              // partials of the previous kernel (0: nothing to judge)
+    int first = 0;            // work index of the launch's first tile (kernels that run in several launches)
 };
 
 // Sum n partials in a fixed order and judge iterate c (one workgroup).

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
     // s = 6, without residual: 4.2 us; 3.8 so, as before tiles had an order).
     asm volatile("" ::"s"(xin), "s"(f), "s"(g.walk.ntx), "s"(g.walk.strip.d), "s"(g.walk.last.d), "s"(g.ox), "s"(g.nx),
                  "s"(g.ld), "s"(s), "s"(g.hh));
-    const int tile = xcd_tile(blk, nblk);
+    const int tile = red.first + xcd_tile(blk, nblk);
     int bi, bj;
     tile_pos(g.walk, tile, bi, bj);
     const int r0 = axis_origin(g.ny, TY, g.oy, bi);
@@ -139,19 +139,37 @@ __global__ __launch_bounds__(kNT) void k_cycle2d(Geom2 g, const T *__restrict__ 
 // costs launches after the verdict a tile load each, little on such grids.
 // ============================================================================
 template <typename T, int C, int R, int W, bool RES, bool ISO, bool FEW>
+__device__ __forceinline__ void cycle2d_reg(const Geom2 &g, const T *__restrict__ f, const T *__restrict__ xin,
+                                            T *__restrict__ xout, int nsub, const Red &red, double tol, int first)
+{
+    constexpr int NT = 64 * W;
+    if (RES && !judged_start<NT, FEW>(red, tol)) return;
+    const int blk = judged_block<RES>();
+    const int tile = first + xcd_tile(blk, judged_blocks<RES>());
+    auto stop = [&] { return RES && FEW && stopped(red.ctrl, red.c); };
+    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, 0>(g, tile, f, xin, xout, nsub, stop);
+    if (RES && FEW && rsq < 0.0) return;
+    if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
+}
+
+template <typename T, int C, int R, int W, bool RES, bool ISO, bool FEW>
 __global__ __launch_bounds__(64 * W, (min_waves_2d<T, C, R>())) void k_cycle2d_reg(Geom2 g, const T *__restrict__ f,
                                                         const T *__restrict__ xin,
                                                         T *__restrict__ xout, int nsub, Red red,
                                                         double tol)
 {
-    constexpr int NT = 64 * W;
-    if (RES && !judged_start<NT, FEW>(red, tol)) return;
-    const int blk = judged_block<RES>();
-    const int tile = xcd_tile(blk, judged_blocks<RES>());
-    auto stop = [&] { return RES && FEW && stopped(red.ctrl, red.c); };
-    const double rsq = reg_tile_2d<T, C, R, W, RES, ISO, 0>(g, tile, f, xin, xout, nsub, stop);
-    if (RES && FEW && rsq < 0.0) return;
-    if (RES) post_partial<NT>(rsq, &red.part_cur[blk]);
+    cycle2d_reg<T, C, R, W, RES, ISO, FEW>(g, f, xin, xout, nsub, red, tol, 0);
+}
+
+// One of several launches of a cycle, from tile red.first on (asked for in
+// every cycle, that took 0.1 to 0.2 us of one without residual).
+template <typename T, int C, int R, int W, bool RES, bool ISO>
+__global__ __launch_bounds__(64 * W, (min_waves_2d<T, C, R>())) void k_cycle2d_sliced(Geom2 g, const T *__restrict__ f,
+                                                        const T *__restrict__ xin,
+                                                        T *__restrict__ xout, int nsub, Red red,
+                                                        double tol)
+{
+    cycle2d_reg<T, C, R, W, RES, ISO, false>(g, f, xin, xout, nsub, red, tol, red.first);
 }
 
 // ============================================================================
@@ -284,11 +302,18 @@ template <typename T, int C, int R, int W, bool FEW>
 hipError_t cyc2_reg(const Geom2 &g, int s, bool res, const void *f, const void *xin, void *xout,
                     const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
     auto go = [&](auto kernel) {
-        kernel<<<nb, 64 * W, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
-        return hipGetLastError();
+        return tile_launches(g, red, res, 64 * W, [&](const Red &r, unsigned nb) {
+            kernel<<<nb, 64 * W, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, r, tol);
+            return hipGetLastError();
+        });
     };
+    if constexpr (!FEW) {
+        if (!one_launch((int64_t)g.ntx * g.nty + 1, 64 * W)) {
+            if (res) return g.iso ? go(k_cycle2d_sliced<T, C, R, W, true, true>) : go(k_cycle2d_sliced<T, C, R, W, true, false>);
+            return g.iso ? go(k_cycle2d_sliced<T, C, R, W, false, true>) : go(k_cycle2d_sliced<T, C, R, W, false, false>);
+        }
+    }
     if (res) return g.iso ? go(k_cycle2d_reg<T, C, R, W, true, true, FEW>) : go(k_cycle2d_reg<T, C, R, W, true, false, FEW>);
     return g.iso ? go(k_cycle2d_reg<T, C, R, W, false, true, FEW>) : go(k_cycle2d_reg<T, C, R, W, false, false, FEW>);
 }
@@ -314,18 +339,14 @@ hipError_t cyc2(const Geom2 &g, int s, bool res, const void *f, const void *xin,
         }
     }
     if constexpr (lds_shape(TX, TY)) {
-        const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
-        const T *F = (const T *)f;
-        const T *XI = (const T *)xin;
-        T *XO = (T *)xout;
-        if (res) {
-            if (g.iso) k_cycle2d<T, TX, TY, true, true><<<nb, kNT, 0, st>>>(g, F, XI, XO, s, red, tol);
-            else k_cycle2d<T, TX, TY, true, false><<<nb, kNT, 0, st>>>(g, F, XI, XO, s, red, tol);
-        } else {
-            if (g.iso) k_cycle2d<T, TX, TY, false, true><<<nb, kNT, 0, st>>>(g, F, XI, XO, s, red, tol);
-            else k_cycle2d<T, TX, TY, false, false><<<nb, kNT, 0, st>>>(g, F, XI, XO, s, red, tol);
-        }
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            return tile_launches(g, red, res, kNT, [&](const Red &r, unsigned nb) {
+                kernel<<<nb, kNT, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, r, tol);
+                return hipGetLastError();
+            });
+        };
+        if (res) return g.iso ? go(k_cycle2d<T, TX, TY, true, true>) : go(k_cycle2d<T, TX, TY, true, false>);
+        return g.iso ? go(k_cycle2d<T, TX, TY, false, true>) : go(k_cycle2d<T, TX, TY, false, false>);
     }
     return hipErrorInvalidValue;  // excluded beforehand by cycle2d_runnable
 }
@@ -352,6 +373,7 @@ hipError_t cyc1(const Geom1 &g, int s, bool res, const void *f, const void *xin,
                 const Red &red, double tol, hipStream_t st)
 {
     const unsigned nb = (unsigned)cycle1d_blocks(g) + (res ? 1 : 0);
+    if (!one_launch(nb, kNT)) return hipErrorInvalidConfiguration;
     if (res) k_cycle1d<T, TT, true><<<nb, kNT, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
     else k_cycle1d<T, TT, false><<<nb, kNT, 0, st>>>(g, (const T *)f, (const T *)xin, (T *)xout, s, red, tol);
     return hipGetLastError();
@@ -426,6 +448,7 @@ static hipError_t sw2(const Geom2 &g, bool res, const void *f, const void *xin, 
                       const Red &red, double tol, hipStream_t st)
 {
     const unsigned nb = (unsigned)sweep2d_blocks(g) + (res ? 1 : 0);
+    if (!one_launch(nb, kNT)) return hipErrorInvalidConfiguration;
     const T *F = (const T *)f;
     const T *XI = (const T *)xin;
     T *XO = (T *)xout;
@@ -450,6 +473,7 @@ hipError_t launch_resid2d(int dt, const Geom2 &g, const void *f, const void *x, 
                           double *part, hipStream_t st)
 {
     const unsigned nb = (unsigned)sweep2d_blocks(g);
+    if (!one_launch(nb, kNT)) return hipErrorInvalidConfiguration;
     const Red red{part, nullptr, nullptr, 0, 0};
     if (dt == F64)
         k_sweep2d<double, true, true, false><<<nb, kNT, 0, st>>>(

@@ -31,6 +31,36 @@ struct Geom1 {
     double w1;           // 1/h^2
 };
 
+// The count of a launch's threads is 32 bits wide and wraps without an error.
+inline bool one_launch(int64_t blocks, int threads) { return blocks * threads <= (int64_t)UINT32_MAX; }
+
+// Work of `blocks` workgroups in as many launches as it takes, go(first
+// workgroup, how many).
+template <typename Go>
+hipError_t in_launches(int64_t blocks, int threads, Go go)
+{
+    const int64_t most = one_launch(blocks + 1, threads) ? blocks : ((int64_t)1 << 31) / threads;
+    for (int64_t first = 0; first < blocks; first += most) {
+        const hipError_t e = go(first, blocks - first < most ? blocks - first : most);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// A cycle over the tiles of g by workgroups of `threads`, one a tile and, with
+// a residual (res), one that judges, in the first launch: go(red, workgroups).
+template <typename Go>
+hipError_t tile_launches(const Geom2 &g, const Red &red, bool res, int threads, Go go)
+{
+    return in_launches((int64_t)g.ntx * g.nty, threads, [&](int64_t first, int64_t n) {
+        Red r = red;
+        r.first = (int)first;
+        if (res) r.part_cur += first;
+        if (first > 0) r.nb_prev = 0;
+        return go(r, (unsigned)(n + (res ? 1 : 0)));
+    });
+}
+
 bool cycle2d_supported(int tx, int ty);
 // false when the tile shape has no kernel for this grid (a 128 extent needs
 // the register kernel and a grid of at least one full tile)
@@ -112,7 +142,9 @@ bool solve_vc_wg_supported(const GeomVC &g, int s);
 hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
                               int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls,
                               hipStream_t st);
-int64_t cycle_vc_blocks(const GeomVC &g);
+inline int64_t cycle_vc_blocks(const GeomVC &g) { return (int64_t)g.ntx * g.nty; }
+// whether launch_cycle_vc can run the cycle (the batched engine runs any)
+bool cycle_vc_one_launch(const GeomVC &g);
 int64_t sweep_vc_blocks(const GeomVC &g);
 hipError_t launch_cycle_vc(const GeomVC &g, int s, bool res, const double *f, const double *xin,
                            double *xout, const Red &red, double tol, hipStream_t st);

@@ -88,6 +88,7 @@ int64_t resid2d_mixed_blocks(const Geom2 &g)
 hipError_t launch_resid2d_f64_to_f32(const Geom2 &g, const double *f, const double *x, float *r32,
                                      float *e32, double *part, hipStream_t st)
 {
+    if (!one_launch(resid2d_mixed_blocks(g), 256)) return hipErrorInvalidConfiguration;
     k_resid2d_f64_to_f32<<<(unsigned)resid2d_mixed_blocks(g), 256, 0, st>>>(g, f, x, r32, e32, part);
     return hipGetLastError();
 }

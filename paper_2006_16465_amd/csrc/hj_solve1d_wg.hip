@@ -337,8 +337,10 @@ hipError_t launch_batch_t(int tt, const WgProb *probs, int64_t nprob, int64_t ma
     const unsigned nth = 64u * (unsigned)max_nt;
     auto go = [&](auto kernel) -> hipError_t {
         if (hipError_t e = allow_lds(kernel, lds); e != hipSuccess) return e;
-        kernel<<<(unsigned)nprob, nth, lds, st>>>(probs, s, c_begin, c_end, maxc, tol, ev, ctrls);
-        return hipGetLastError();
+        return in_launches(nprob, (int)nth, [&](int64_t first, int64_t n) {
+            kernel<<<(unsigned)n, nth, lds, st>>>(probs + first, s, c_begin, c_end, maxc, tol, ev, ctrls + first);
+            return hipGetLastError();
+        });
     };
     switch (tt) {
     case 64: return max_nt <= 8 ? go(k_solve1d_wg_batch<T, 64, 8>) : go(k_solve1d_wg_batch<T, 64, 16>);

@@ -96,8 +96,10 @@ template <int TX, int TY>
 hipError_t cyc_vc(const GeomVC &g, int s, bool res, const double *f, const double *xin, double *xout,
                   const Red &red, double tol, hipStream_t st)
 {
-    const unsigned nb = (unsigned)((int64_t)g.ntx * g.nty) + (res ? 1 : 0);
+    const unsigned nb = (unsigned)cycle_vc_blocks(g) + (res ? 1 : 0);
     constexpr int NT = vc_threads<TX, TY>();
+    static_assert(NT == 8 * TY, "cycle_vc_one_launch counts them so");
+    if (!one_launch(nb, NT)) return hipErrorInvalidConfiguration;
     auto go = [&](auto kernel) {
         kernel<<<nb, NT, 0, st>>>(g, f, xin, xout, s, red, tol);
         return hipGetLastError();
@@ -122,7 +124,7 @@ hipError_t launch_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, c
 
 }  // namespace
 
-int64_t cycle_vc_blocks(const GeomVC &g) { return (int64_t)g.ntx * g.nty; }
+bool cycle_vc_one_launch(const GeomVC &g) { return one_launch(cycle_vc_blocks(g) + 1, 8 * g.ty); }
 int64_t sweep_vc_blocks(const GeomVC &g) { return ((int64_t)g.nx * g.ny + kNT - 1) / kNT; }
 
 hipError_t launch_cycle_vc(const GeomVC &g, int s, bool res, const double *f, const double *xin,
@@ -139,6 +141,7 @@ hipError_t launch_sweep_vc(const GeomVC &g, bool res, const double *f, const dou
                            const Red &red, double tol, hipStream_t st)
 {
     const unsigned nb = (unsigned)sweep_vc_blocks(g) + (res ? 1 : 0);
+    if (!one_launch(nb, kNT)) return hipErrorInvalidConfiguration;
     if (res) k_sweep2d_vc<true, true><<<nb, kNT, 0, st>>>(g, f, xin, xout, red, tol);
     else k_sweep2d_vc<false, true><<<nb, kNT, 0, st>>>(g, f, xin, xout, red, tol);
     return hipGetLastError();
@@ -148,6 +151,7 @@ hipError_t launch_resid_vc(const GeomVC &g, const double *f, const double *x, do
                            double *part, hipStream_t st)
 {
     const unsigned nb = (unsigned)sweep_vc_blocks(g);
+    if (!one_launch(nb, kNT)) return hipErrorInvalidConfiguration;
     const Red red{part, nullptr, nullptr, 0, 0};
     k_sweep2d_vc<true, false><<<nb, kNT, 0, st>>>(g, f, x, r_out, red, -1.0);
     return hipGetLastError();
@@ -156,8 +160,9 @@ hipError_t launch_resid_vc(const GeomVC &g, const double *f, const double *x, do
 hipError_t launch_grad_a_vc(const GeomVC &g, const double *u, const double *lam, int nb,
                             int64_t bstride, double *grad, int64_t ldg, hipStream_t st)
 {
-    const int64_t total = (int64_t)(g.nx + 2) * (g.ny + 2);
-    k_grad_a_vc<<<(unsigned)((total + kNT - 1) / kNT), kNT, 0, st>>>(g, u, lam, nb, bstride, grad, ldg);
+    const int64_t total = (int64_t)(g.nx + 2) * (g.ny + 2), nb64 = (total + kNT - 1) / kNT;
+    if (!one_launch(nb64, kNT)) return hipErrorInvalidConfiguration;
+    k_grad_a_vc<<<(unsigned)nb64, kNT, 0, st>>>(g, u, lam, nb, bstride, grad, ldg);
     return hipGetLastError();
 }
 

@@ -474,3 +474,19 @@ def test_vc_one_workgroup_solves_of_very_many_right_hand_sides(nb):
     st = hj.load().hj_solve_vc_2d(ctypes.byref(pr), f.data_ptr(), u.data_ptr(), ctypes.byref(p), hj._stream(f), None)
     assert st == hj.HJ_OK, hj.last_error()
     assert torch.equal(u, _one_column(a, f, torch.zeros_like(f), 0.1, s * cycles))
+
+
+def test_vc_cycles_of_more_threads_than_a_launch_counts():
+    """16 x 16 tiles a point apart: with s = 1 a cycle is one classical sweep, whatever their number."""
+    n, ov = 5830, 15
+    assert hj.axis_tiles(n, 16, ov) ** 2 * 128 > 2 ** 32
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    a = torch.rand(n + 2, n + 2, dtype=torch.float64, device="cuda", generator=gen) + 0.5
+    f = torch.randn(n, n, dtype=torch.float64, device="cuda", generator=gen)
+    say("threads, vc")
+    for tol in (0.0, 1e-100):
+        kw = dict(rel_tol=tol, max_cycles=3, allow_not_converged=True)
+        X, Y = torch.zeros_like(f), torch.zeros_like(f)
+        hj.solve_vc_2d(a, f, X, 1.0 / (n + 1), tile=(16, 16), s=1, overlap=(ov, ov), **kw)
+        hj.solve_vc_2d(a, f, Y, 1.0 / (n + 1), method="global", **kw)
+        assert torch.equal(X, Y), tol

@@ -702,3 +702,50 @@ def test_many_tiles_shape_matches_oracle(orc, n, iso):
             hj.solve_2d(dev(f), X, hx=hx, hy=hy, tile=(32, 128), s=s, overlap=ov, rel_tol=tol, max_cycles=2,
                         allow_not_converged=True)
             assert np.array_equal(host(X), want), (s, ov, tol)
+
+
+# ------------------------------------------------------------------ cycles of more than 2^32 threads
+
+@pytest.mark.parametrize("n,tile,ov,lds", [((5860, 5850), (32, 32), (31, 31), False), ((4130, 4120), (16, 16), (15, 15), True),
+                                           ((4150, 4200), (32, 64), (31, 63), False)])
+def test_cycles_of_more_threads_than_a_launch_counts(n, tile, ov, lds):
+    """Tiles a point apart: with s = 1 a cycle is one classical sweep, whatever their number."""
+    nx, ny = n
+    tiles = hj.axis_tiles(nx, tile[0], ov[0]) * hj.axis_tiles(ny, tile[1], ov[1])
+    assert tiles * (256 if lds else 4 * tile[1]) > 2 ** 32
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    f = torch.randn(ny, nx, dtype=torch.float64, device="cuda", generator=gen)
+    x0 = torch.randn(ny, nx, dtype=torch.float64, device="cuda", generator=gen)
+    h = 1.0 / (nx + 1)
+    say(f"threads {n} {tile} o={ov}")
+    for tol in (0.0, 1e-100):
+        kw = dict(rel_tol=tol, max_cycles=3, allow_not_converged=True)
+        X, Y = x0.clone(), x0.clone()
+        info = hj.solve_2d(f, X, h, tile=tile, s=1, overlap=ov, lds_kernel=lds, **kw)
+        ref = hj.solve_2d(f, Y, h, method="global", **kw)
+        assert torch.equal(X, Y), tol
+        # sums of 3.4e7 squares in two orders, each by at least 15 levels of partial sums
+        assert abs(info.r0_norm - ref.r0_norm) <= 1e-11 * ref.r0_norm
+        assert abs(info.rel_residual - ref.rel_residual) <= 2e-11 * ref.rel_residual
+
+
+def test_batch_of_more_threads_than_a_launch_counts():
+    n, ov = 4140, 31
+    assert 2 * hj.axis_tiles(n, 32, ov) ** 2 * 128 > 2 ** 32
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    f = torch.randn(2, n, n, dtype=torch.float64, device="cuda", generator=gen)
+    X = torch.zeros_like(f)
+    say("threads, batch")
+    hj.solve_batched([(f[i], X[i], 1.0 / (n + 1)) for i in range(2)], rel_tol=0.0, tile=(32, 32), s=1, overlap=(ov, ov),
+                     max_cycles=3)
+    for i in range(2):
+        Y = torch.zeros_like(f[i])
+        hj.solve_2d(f[i], Y, 1.0 / (n + 1), method="global", rel_tol=0.0, max_cycles=3)
+        assert torch.equal(X[i], Y), i
+
+
+def test_1d_cycles_of_more_threads_than_a_launch_counts_are_refused():
+    n = 2 ** 26 + 2 ** 10
+    f = torch.zeros(n, dtype=torch.float32, device="cuda")
+    with pytest.raises(hj.HJError):
+        hj.solve_1d(f, torch.zeros_like(f), 1.0 / (n + 1), tile=64, s=1, overlap=63, rel_tol=0.0, max_cycles=1)
