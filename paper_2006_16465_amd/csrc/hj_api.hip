@@ -359,8 +359,8 @@ hj::Geom2 make_geom2(int64_t nx, int64_t ny, int64_t ld, double hx, double hy, c
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
     const int64_t tile_bytes = 24 * (int64_t)g.tx * g.ty;
     // in double: the products of the largest accepted axes leave 64 bits
-    const double moved = dt == HJ_F64 ? (double)g.ntx * g.nty * tile_bytes : 12.0 * nx * ny;
-    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, moved > hj::kLargeBytes);
+    const bool large = dt == HJ_F64 ? (double)g.ntx * g.nty * tile_bytes > hj::kLargeF64 : 12.0 * nx * ny > hj::kLargeF32;
+    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, large);
     g.iso = hx == hy;
     g.reg = (p.flags & HJ_FLAG_LDS_KERNEL) ? 0 : 1;
     g.hh = hx * hx;
@@ -412,7 +412,7 @@ hj::GeomVC make_geom_vc(const hj_vc_problem &pr, const hj_params &p)
     g.ntx = hj::axis_count(g.nx, g.tx, g.ox);
     g.nty = hj::axis_count(g.ny, g.ty, g.oy);
     const int64_t tile_bytes = 32 * (int64_t)g.tx * g.ty;
-    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, (double)g.ntx * g.nty * tile_bytes > hj::kLargeBytes);
+    g.walk = hj::make_walk(g.ntx, g.nty, tile_bytes, (double)g.ntx * g.nty * tile_bytes > hj::kLargeF64);
     g.a = pr.a;
     g.lda = pr.lda;
     g.ihx2 = 1.0 / (pr.hx * pr.hx);

@@ -105,14 +105,16 @@ struct Walk {
 // 138 / 136, 64 x 128 o = 22 147 / 145.
 //
 // FP64 grids are large where their tiles move more than the memory-side cache
-// holds (kLargeBytes), the parts that overlap counted each time: 3000^2, 32 x 32,
-// s = 4, overlap 6 (330 MB of tiles, 216 MB of grid), without residual 47 / 42 us.
-// FP32 grids where the grid itself does: at 4096^2 (201 MB of grid), 32 x 32
-// tiles, s = 4, overlap 6 (306 MB of tiles) 44.0 / 46.5, s = 2, overlap 2
-// 39.3 / 41.7, other shapes alike; beyond, s = 4, 5200^2 105.6 / 103.5, 6500^2
-// 166.7 / 161.6.  Strips are as wide for FP32 as for FP64 (tile_bytes of
-// FP64 points): twice as wide they took 2 % more at 6000^2, s = 2 and 4.
-constexpr double kLargeBytes = 256 << 20;
+// holds (kLargeF64), the parts that overlap counted each time: 3000^2, 32 x 32,
+// s = 4, overlap 6 (330 MB of tiles, 216 MB of grid), without residual 47 / 42 us;
+// 3300^2, s = 2, overlap 2 (297 MB) 58.4 / 55.8.  FP32 grids where the grid
+// itself comes near it (kLargeF32): 32 x 32 tiles, without residual, s = 2,
+// overlap 2 and s = 4, overlap 6, 4096^2 (201 MB) 36.1 / 39.0 and 38.8 / 42.6,
+// 4200^2 41.5 / 44.5 and 48.2 / 48.9, 4400^2 (232 MB) 56.5 / 54.2 and 63.6 /
+// 60.9, 4800^2, s = 2, 75.7 / 73.1; 3600^2 alike; 64-wide tiles within 1 % at
+// 4096^2.  Strips are as wide for FP32 as for FP64 (tile_bytes of FP64 points):
+// twice as wide they took 2 % more at 6000^2, s = 2 and 4.
+constexpr double kLargeF64 = 256 << 20, kLargeF32 = 208 << 20;
 
 inline Walk make_walk(int ntx, int nty, int64_t tile_bytes, bool large)
 {
