@@ -395,8 +395,9 @@ hj_status hj_autotune_batch(const hj_problem *probs, int64_t nprob, hj_dtype dty
  * HJ_FLAG_LDS_KERNEL, the LDS ping-pong tile: same iterates either way.
  * Hierarchical solves of at most 64 x 64 points whose overlaps reach 2 s - 2
  * (on each axis of more than one tile) run whole in one workgroup per
- * right-hand side, to the same iterates, unless HJ_FLAG_LDS_KERNEL or
- * HJ_FLAG_LAUNCH_PER_CYCLE asks for a launch per cycle. */
+ * right-hand side, to the same iterates, where that takes less time (wide
+ * grids; others while right-hand sides and sweeps are few), unless
+ * HJ_FLAG_LDS_KERNEL or HJ_FLAG_LAUNCH_PER_CYCLE asks for a launch per cycle. */
 typedef struct hj_vc_problem {
     int64_t nx, ny;        /* interior grid */
     int64_t ld;            /* leading dimension of f, u, lam (elements, >= nx) */

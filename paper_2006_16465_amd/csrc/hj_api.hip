@@ -1917,7 +1917,8 @@ hj_status hj_solve_vc_2d(const hj_vc_problem *prob, const double *f, double *u, 
     DevScratch &S = g_scr[dev];
     std::lock_guard<std::mutex> lock(S.mu);
     if (p->method == HJ_HIERARCHICAL && !(p->flags & HJ_FLAG_LAUNCH_PER_CYCLE) &&
-        hj::solve_vc_wg_supported(make_geom_vc(*prob, *p), p->s))
+        hj::solve_vc_wg_supported(make_geom_vc(*prob, *p), p->s) &&
+        hj::solve_vc_wg_faster(make_geom_vc(*prob, *p), p->s, prob->batch))
         return solve_vc_wg(*prob, f, u, *p, (hipStream_t)stream, g_bat[dev], infos);
     if (p->method == HJ_HIERARCHICAL && (prob->batch > 1 || !hj::cycle_vc_one_launch(make_geom_vc(*prob, *p))))
         return solve_vc_batched(*prob, f, u, *p, (hipStream_t)stream, dev, S, infos);

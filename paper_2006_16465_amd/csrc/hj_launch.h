@@ -139,6 +139,8 @@ struct GeomVC {
 // as in launch_solve1d_wg.  Supported: grids up to 64 x 64 whose cycle is s
 // sweeps of the whole grid, without HJ_FLAG_LDS_KERNEL (g.reg).
 bool solve_vc_wg_supported(const GeomVC &g, int s);
+// whether they take less time so than by the tile kernels
+bool solve_vc_wg_faster(const GeomVC &g, int s, int64_t batch);
 hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
                               int64_t c_begin, int64_t c_end, int64_t maxc, double tol, bool every, Ctrl *ctrls,
                               hipStream_t st);

@@ -5,6 +5,8 @@
 // The operator, its face weights and the cycle body live in hj_vc_tile.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "hj_launch.h"
 #include "hj_vc_tile.h"
 #include "hj_solve_vc_wg.h"
@@ -166,19 +168,45 @@ hipError_t launch_grad_a_vc(const GeomVC &g, const double *u, const double *lam,
     return hipGetLastError();
 }
 
+// Rows a wavefront: the fewest that hold the grid in eight wavefronts.
+static int vc_wg_rows(int ny) { return ny <= 16 ? 2 : ny <= 24 ? 3 : ny <= 32 ? 4 : ny <= 48 ? 6 : 8; }
+
 // Grids of at most 64 x 64 points whose cycle is s sweeps of the whole grid.
-// There a sweep by one workgroup (0.38 us at 64 x 64) takes no longer than one
-// by the workgroup of a 64 x 64 tile, and the cycle's launch, its loads and
-// stores and the tiles' overlap fall away: us a cycle with a launch each and
-// here, s = 8, overlap 14: one right-hand side at 64 x 64 (64 x 32 tiles) 7.8
-// and 3.8, 16 of them 11.3 and 3.8, 1024 of them 48 and 17; four at 20 x 20
-// (32 x 32 tiles) 11.4 and 2.5; 1024 at 30 x 30 20 and 8.9.  Higher grids do
-// not fit a SIMD's registers with two wavefronts (64 x 128: 13.9 and 10.1 with
-// 16 right-hand sides, but slower with one), nor wider ones a row a wavefront.
+// Higher ones do not fit a SIMD's registers with two wavefronts (64 x 128:
+// 13.9 and 10.1 us a cycle of 16 right-hand sides by tiles and here, but slower
+// with one), nor wider ones a row a wavefront.
 bool solve_vc_wg_supported(const GeomVC &g, int s)
 {
     auto whole = [s](int tiles, int overlap) { return tiles == 1 || overlap >= 2 * ((int64_t)s - 1); };
     return g.reg && g.nx <= 64 && g.ny <= 64 && whole(g.ntx, g.ox) && whole(g.nty, g.oy);
+}
+
+// Whether they run here: s sweeps must not cost more beyond the tile kernels'
+// s sweeps than what those pay for a cycle's launches, loads and stores.  In us,
+// for b right-hand sides:
+// - a sweep here takes its chain, by the rows of a wavefront, or its issue, 24
+//   ps a row and right-hand side, of 64 lanes whatever the grid's width;
+// - a sweep of the tiles takes their chain, by a tile's points (the LDS body's
+//   is longer), or 0.34 ps a point;
+// - a cycle of the tiles takes 1 and more beside its sweeps with one right-hand
+//   side, and with several (a launch to judge them) 5 and what grows with them.
+// So wide grids run here (us a cycle by tiles / here, 64 x 64, s = 8: one
+// right-hand side 8.8 / 3.9, 64 14.0 / 4.0, 8 192 248 / 134), narrow or low
+// ones while right-hand sides or sweeps are few (3 x 64, s = 8: 512 of them
+// 15.1 / 9.2, 2 048 26.7 / 35.7; 16 x 16: 2 048, s = 8 14.7 / 9.6, s = 32 20.0 /
+// 29.6; 32 x 32: 2 048, s = 8 23.1 / 16.3, s = 32 40.0 / 53.6).  The numbers were
+// fitted to 891 pairs of times over 26 shapes, 1 to 8 192 right-hand sides and
+// s = 3 to 128; the way taken is within 5 % of the faster one in all but 13, and 27
+// % from it at most (32 x 64 as one tile, one right-hand side, s = 20).
+bool solve_vc_wg_faster(const GeomVC &g, int s, int64_t batch)
+{
+    const double b = (double)batch, pts = (double)g.tx * g.ty;
+    const int rows = vc_wg_rows(g.ny), padded = (g.ny + rows - 1) / rows * rows;
+    const double here = std::max(0.14 + 0.023 * rows, 2.4e-5 * b * padded);
+    const double chain = (0.13 + 5.3e-5 * pts) * (vc_reg(g) ? 1.0 : 1.2);
+    const double tiles = std::max(chain, 3.4e-7 * b * g.ntx * g.nty * pts);
+    const double cycle = batch == 1 ? 0.91 + 7.3e-4 * pts : 4.9 + b * (1.3e-3 + 3.9e-6 * g.nx * g.ny);
+    return s * (here - tiles) <= cycle;
 }
 
 hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, int s, const double *f, double *u,
@@ -191,12 +219,13 @@ hipError_t launch_solve_vc_wg(const GeomVC &g, int64_t batch, int64_t stride, in
     auto at = [&](auto launch) {
         return launch(g, batch, stride, s, f, u, c_begin, c_end, maxc, tol, every, ctrls, st);
     };
-    // rows a wavefront: the fewest that hold the grid in eight
-    if (g.ny <= 16) return at(launch_vc_wg<2>);
-    if (g.ny <= 24) return at(launch_vc_wg<3>);
-    if (g.ny <= 32) return at(launch_vc_wg<4>);
-    if (g.ny <= 48) return at(launch_vc_wg<6>);
-    return at(launch_vc_wg<8>);
+    switch (vc_wg_rows(g.ny)) {
+    case 2: return at(launch_vc_wg<2>);
+    case 3: return at(launch_vc_wg<3>);
+    case 4: return at(launch_vc_wg<4>);
+    case 6: return at(launch_vc_wg<6>);
+    default: return at(launch_vc_wg<8>);
+    }
 }
 
 }  // namespace hj

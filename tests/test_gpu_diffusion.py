@@ -490,3 +490,24 @@ def test_vc_cycles_of_more_threads_than_a_launch_counts():
         hj.solve_vc_2d(a, f, X, 1.0 / (n + 1), tile=(16, 16), s=1, overlap=(ov, ov), **kw)
         hj.solve_vc_2d(a, f, Y, 1.0 / (n + 1), method="global", **kw)
         assert torch.equal(X, Y), tol
+
+
+# grids and right-hand sides on both sides of where the whole solve in one
+# workgroup takes less time than the tile kernels
+@pytest.mark.parametrize("n,tile,s", [((3, 64), (16, 64), 8), ((16, 16), (16, 16), 32), ((20, 20), (32, 32), 32),
+                                      ((32, 48), (32, 32), 16)])
+@pytest.mark.parametrize("nb", [1, 2, 300, 3000])
+def test_vc_solves_are_the_same_by_either_way(n, tile, s, nb):
+    nx, ny = n
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    a = torch.rand(ny + 2, nx + 2, dtype=torch.float64, device="cuda", generator=gen) + 0.5
+    f = torch.randn(nb, ny, nx, dtype=torch.float64, device="cuda", generator=gen)
+    say(f"vc either way {n} s={s} x {nb}")
+    for tol, cap in ((0.0, 3), (1e-3, 40)):
+        out = []
+        for per_cycle in (False, True):
+            U = torch.zeros_like(f)
+            infos = hj.solve_vc_2d(a, f, U, 1.0 / (nx + 1), tile=tile, s=s, overlap=tuple(min(2 * s - 2, t - 1) for t in tile),
+                                   rel_tol=tol, max_cycles=cap, allow_not_converged=True, launch_per_cycle=per_cycle)
+            out.append(([i.cycles for i in infos], U))
+        assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1]), tol
