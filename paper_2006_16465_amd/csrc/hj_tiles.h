@@ -78,27 +78,10 @@ constexpr int min_waves_2d()
 constexpr int kDppRowShr1 = 0x111;  // lane i <- lane i - 1 of its 16-lane row
 constexpr int kDppRowShl1 = 0x101;  // lane i <- lane i + 1 of its 16-lane row
 
-// Lanes whose source falls outside the 16-lane row receive 0 (bound_ctrl).
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift(double v)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_shift(float v)
-{
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-
-// Shifted like dpp_shift, but lanes whose source lies outside the 16-lane
-// row keep `old` (bound_ctrl off): a register that holds the frozen x-halo
-// in the first (row_shr) or last (row_shl) lane of each row keeps it there
-// while every other lane receives its neighbour's value.
+// The neighbour's value; lanes whose source lies outside the 16-lane row keep
+// `old` (bound_ctrl off): a register that holds the frozen x-halo in the first
+// (row_shr) or last (row_shl) lane of each row keeps it there while every other
+// lane receives its neighbour's value.
 template <int CTRL>
 __device__ __forceinline__ double dpp_keep(double old, double v)
 {
