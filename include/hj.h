@@ -134,8 +134,9 @@ typedef struct hj_params {
     int32_t method;      /* hj_method */
     int64_t max_cycles;  /* >= 1: cycles (HJ_GLOBAL: sweeps) allowed */
     int32_t check_every; /* cycles enqueued between host polls of the device-side
-                            convergence flag; 0 = adaptive (at most about 0.5 ms of
-                            GPU work per poll).  Does not change results. */
+                            convergence flag; 0 = adaptive (4 cycles, or as many
+                            as take about 0.06 to 0.5 ms of GPU time if that is
+                            more).  Does not change results. */
     int32_t flags;       /* 0, or HJ_FLAG_LDS_KERNEL | HJ_FLAG_LAUNCH_PER_CYCLE */
     double rel_tol;      /* > 0: stop at the first cycle c with ||r_c|| <= rel_tol ||r_0||.
                             <= 0: run exactly max_cycles cycles with no residual

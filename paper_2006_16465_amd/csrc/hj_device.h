@@ -100,9 +100,9 @@ struct Walk {
 // the walk, about 64 tiles at a time, so the overlap (or halo) rows that
 // vertical neighbours share are read again while its 4 MB L2 still holds them;
 // row by row over the whole grid they come back after tiles_x tiles.  Measured
-// at 4096^2, us per FP64 cycle, whole rows / strips: 32 x 32 tiles 97 / 90
-// (3.1 MB a row; strips of 16, 24 and 43 columns alike), 64 x 64 o = 22
-// 138 / 136, 64 x 128 o = 22 147 / 145.
+// at 4096^2, us per FP64 cycle with residual, whole rows / strips: 32 x 32
+// tiles 99 / 88 (3.1 MB a row; strips of 16, 24 and 43 columns alike), 64 x 32
+// o = 14 126 / 117, 64 x 64 o = 22 135 / 132, 64 x 128 o = 22 144 / 142.
 //
 // FP64 grids are large where their tiles move more than the memory-side cache
 // holds (kLargeF64), the parts that overlap counted each time: 3000^2, 32 x 32,

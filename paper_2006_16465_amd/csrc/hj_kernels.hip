@@ -292,9 +292,9 @@ constexpr bool lds_shape(int tx, int ty)
 // The FEW shape is taken where the tiles of the ordinary one have no more
 // wavefronts than the chip has SIMDs (4 on each of 256 CUs): each then runs
 // alone on its SIMD and a sweep takes as long as its own chain.  Measured, us
-// per FP64 cycle, ordinary / FEW shape: 32 x 32 tiles at s = 16, 512^2 (512
-// wavefronts) 6.9 / 5.8, 4096^2 (32 768) 90 / 98; 64 x 64 at s = 10, 512^2
-// (484) 8.5 / 8.3, 1024^2 (1 936) 12.0 / 12.3; 32 x 64 at s = 32, 1024^2
+// per FP64 cycle with residual, ordinary / FEW shape: 32 x 32 tiles at s = 16,
+// 512^2 (512 wavefronts) 7.4 / 6.5, 4096^2 (32 768) 90 / 98; 64 x 64 at s = 10,
+// 512^2 (484) 8.7 / 8.4, 1024^2 (1 936) 12.0 / 12.3; 32 x 64 at s = 32, 1024^2
 // (3 268) 19.3 / 23.6.
 constexpr int64_t kSimds = 1024;
 

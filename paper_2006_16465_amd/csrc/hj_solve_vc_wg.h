@@ -7,8 +7,8 @@
 // the tile per sweep after the first, and the tile hands over the points at
 // least s away from it).  So on a grid whose points, right-hand side and face
 // weights fit one workgroup's registers, the cycles are sweeps of the whole
-// grid by that workgroup: no launch, no memory traffic and no halo work
-// between them.  The residual of the iterate a cycle starts from is formed in
+// grid by that workgroup: no launch, no loads and no halo work between them (the
+// iterate a cycle starts from is stored where it may be the one to stop at).  The residual of the iterate a cycle starts from is formed in
 // its first sweep and judged before the next cycle, so the solve stops at the
 // same iterate as the per-cycle path.
 #pragma once
